@@ -93,15 +93,28 @@ struct CacheView {
 int cache_view(const cheb_cache *c, CacheView *v);
 
 // Residual kernel (kernels.hip): x_out[j] = x_in[j] + sum over the ncover
-// offsets delta[c] and entries k < n of w[k] * (the 16-byte vector at
-//   contiguous (super_vecs == kChunkVecs): base[k] + delta[c] + 16 * j bytes;
-//   interleaved: vector v = delta[c] + j of the entry at base[k], placed by
-//   the chunk formula above),
-// for residual vectors j in [vec_begin, vec_begin + n_vec).
+// offsets delta[c] and entries k < n of w[k] * (16-byte vector delta[c] + j
+// of the entry at base[k], placed by the chunk formula above, which is the
+// identity for contiguous entries), for residual vectors j in [vec_begin,
+// vec_begin + n_vec).
 // ncover <= residual_max_cover(); vector indices below 2^31.
 int residual_max_cover();
 int launch_residual(int dtype, int n, const uint64_t *base, const double *w,
                     const int64_t *delta, int ncover, const float *x_in, float *x_out,
                     int64_t vec_begin, int64_t n_vec, int64_t super_vecs, hipStream_t stream);
+
+// The same for several intervals in one launch: interval i adds the next
+// iv[i].ncover offsets of the table of n_delta.  n_iv <= kMaxResIntervals,
+// n_delta <= residual_max_cover(), every n_vec > 0, all tiles of 64 vectors
+// below 2^31.
+struct ResidualInterval {
+  int64_t vec_begin, n_vec;
+  int32_t ncover;
+};
+constexpr int kMaxResIntervals = 8;
+int launch_residual_intervals(int dtype, int n, const uint64_t *base, const double *w,
+                              const int64_t *delta, int n_delta, const ResidualInterval *iv,
+                              int n_iv, const float *x_in, float *x_out, int64_t super_vecs,
+                              hipStream_t stream);
 
 }  // namespace cheb

@@ -29,6 +29,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -290,6 +291,19 @@ int auto_waves(int ns, int no) {
   return std::max(6, (kib + ns / 2) / ns);
 }
 
+// LDS bytes of one block when `blocks` of them are to share a compute unit:
+// an equal share rounded down to the 1280-byte unit LDS is handed out in on
+// gfx950 (a size in between takes the next unit, and one block fewer fits).
+// A share past the 64 KiB a block may have is cut to that, if as many blocks
+// still fit and no more.  Zero when there is no limit or none is possible.
+size_t lds_share(int lds_per_cu, int blocks) {
+  constexpr int kMost = 64 << 10;
+  if (blocks <= 0 || lds_per_cu <= 0) return 0;
+  const int per = lds_per_cu / blocks / 1280 * 1280;
+  if (per <= kMost) return size_t(per);
+  return lds_per_cu / kMost == blocks ? size_t(kMost) : 0;
+}
+
 // Dynamic LDS a block reserves, and never touches, so that about `waves`
 // waves of the kernel share a compute unit (the LDS is what runs out): an
 // equal share of the compute unit's LDS, rounded down to 512 bytes.  Zero
@@ -465,11 +479,11 @@ __global__ __launch_bounds__(kGatherBlock) void gather_kernel(GatherArgs a, char
 // block stack adds sum_k w_k H_k[segment] for every cached segment, so
 //     x_out[j] = x_in[j] + sum_{segments s covering j} sum_k w_k H_k[s, j]
 // can be formed in one pass that reads the history once and never writes
-// the per-module predictions.  One launch covers one interval of the
-// residual on which the set of covering segments is constant (all of it for
-// DiT; the text and image parts for FLUX).  The covering segments travel as
-// byte offsets in the kernel arguments: entry k's element j of segment s is
-// at base[k] + delta[s] + 16 * (vector index of j).  Accumulation is fp64
+// the per-module predictions.  A launch covers the intervals of the residual
+// on which the set of covering segments is constant (all of it for DiT; the
+// text and image parts for FLUX), as many as its tables hold.  The covering
+// segments travel as vector offsets in the kernel arguments: residual vector
+// j takes vector delta[s] + j of the entry at base[k].  Accumulation is fp64
 // (hundreds of terms per element), output fp32.
 
 struct Bf16Dec {
@@ -504,127 +518,234 @@ struct F32Dec {
 };
 
 constexpr int kResCover = 128;
-constexpr int kResBlock = 1024;
+constexpr int kResIntervals = kMaxResIntervals;
+constexpr int kResTile = 64;  // residual vectors per block, one per lane
+
+// One interval's part of a launch: tiles from `tile` on.
+struct ResPart {
+  uint32_t tile;
+  uint32_t vec_begin, n_vec;
+  int32_t first, ncover;  // its covering segments in the delta table
+};
 
 template <int NS>
 struct ResArgs {
   uint64_t base[NS];
   double w[NS];
-  int64_t delta[kResCover];  // bytes (contiguous entries) or vectors (interleaved)
+  int64_t delta[kResCover];  // vectors, from an entry's base to the segment's residual vector 0
+  ResPart part[kResIntervals];
+  int32_t n_part;
   const float *x_in;  // may be null: zero
   float *x_out;
   uint64_t super;
-  uint32_t vec_begin;
-  uint32_t n_vec;
-  int32_t ncover;
 };
 
-// Source vector of residual vector j in covering segment s of the entry at
-// `base`.
+// A tile's vectors of one covering segment: entry k's go to v[k].  The place
+// of the tile's first vector v0 is uniform (scalar arithmetic); a lane adds
+// its own index and, past the end of that vector's chunk, the jump to the entry's
+// next one (64 vectors span at most two chunks; for contiguous entries super
+// is kChunkVecs and there is no jump).
 template <int NS>
-__device__ __forceinline__ const u32x4 *res_src(const ResArgs<NS> &a, bool flat, uint64_t base,
-                                                int32_t s, uint64_t j) {
-  if (flat) return reinterpret_cast<const u32x4 *>(base + uint64_t(a.delta[s]) + j * 16u);
-  return reinterpret_cast<const u32x4 *>(base) + lane_vec(uint64_t(a.delta[s]) + j, a.super);
+__device__ __forceinline__ void res_load(u32x4 (&v)[NS], const ResArgs<NS> &a, uint64_t v0,
+                                         uint32_t lane) {
+  const uint32_t r = uint32_t(v0) & uint32_t(kChunkVecs - 1);
+  const uint64_t off = (v0 >> kChunkShift) * a.super + r;
+  const uint32_t l =
+      lane + (r + lane >= uint32_t(kChunkVecs) ? uint32_t(a.super - uint64_t(kChunkVecs)) : 0u);
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+    // In the global address space: an address made from an integer is
+    // otherwise loaded as a flat one.
+    auto *p = reinterpret_cast<const __attribute__((address_space(1))) char *>(a.base[k] +
+                                                                              off * 16u);
+    v[k] = __builtin_nontemporal_load(
+        reinterpret_cast<const __attribute__((address_space(1))) u32x4 *>(p + l * 16u));
+  }
 }
 
-// Each block starts its walk over the covering segments at a different
-// segment (its index times two, modulo the count), so at any moment the
-// chip's reads spread over many segments instead of all blocks reading the
-// same one: measured 5-10% faster on the FLUX image interval.  Each
-// element's sum is still over every covering segment exactly once.
-template <class Dec, int NS>
-__global__ __launch_bounds__(kResBlock) void residual_kernel(ResArgs<NS> a) {
+// Bound by HBM reads: NS x ncover loads of 1 KiB per tile of 64 residual
+// vectors.  The W waves of a block take the covering segments in turn, U at
+// a time with all their loads ahead of the arithmetic, into fp64 partial
+// sums of the same 64 vectors, and add those up through LDS.  Dividing the
+// segments among waves gives a small residual W times the waves to fill the
+// chip with, and has the blocks in flight read neighbouring kilobytes of a
+// few places at a time rather than 16 KiB runs of every place.  Measured on
+// MI355X against one residual vector per lane of 1024-lane blocks: the
+// FLUX-1024 cache, 6 interleaved entries, 1566 -> 1447 us (6.3 -> 6.8 TB/s);
+// DiT-XL/2 256 for one image (56 segments, 1152 tiles), 3 entries, 66 -> 35
+// us; an eighth of it (144 tiles), 54 -> 10 us.
+template <class Dec, int NS, int W, int U>
+__global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
   constexpr int V = Dec::kVec;
-  const uint32_t i = blockIdx.x * uint32_t(kResBlock) + threadIdx.x;
-  if (i >= a.n_vec) return;
-  const uint64_t j = uint64_t(a.vec_begin) + i;  // residual vector index
+  constexpr uint32_t kThreads = 64u * W;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane = threadIdx.x & 63u;
+  int32_t p = 0;
+  for (int32_t q = 1; q < a.n_part; ++q)
+    if (blockIdx.x >= a.part[q].tile) p = q;
+  const ResPart part = a.part[p];
+  const uint32_t first = (blockIdx.x - part.tile) * uint32_t(kResTile);
+  const uint32_t left = part.n_vec - first;
+  const uint32_t live = left < uint32_t(kResTile) ? left : uint32_t(kResTile);  // vectors here
+  const uint32_t l = lane < live ? lane : live - 1u;  // idle lanes repeat the last vector
+  const uint64_t j0 = uint64_t(part.vec_begin) + first;
+  const int64_t *delta = a.delta + part.first;
+  const int32_t nc = part.ncover;
   double acc[V];
-  if (a.x_in) {
-    const u32x4 *xi = reinterpret_cast<const u32x4 *>(a.x_in + j * V);
 #pragma unroll
-    for (int h = 0; h < V / 4; ++h) {
-      const u32x4 x = xi[h];
+  for (int e = 0; e < V; ++e) acc[e] = 0.0;
+  int32_t c = int32_t(wave) * U;
+  for (; c + U <= nc; c += W * U) {
+    u32x4 v[U][NS];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[4 * h + q] = double(__uint_as_float(x[q]));
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < V; ++e) acc[e] = 0.0;
-  }
-  const bool flat = a.super == uint64_t(kChunkVecs);
-  const int32_t nc = a.ncover;
-  const int32_t start = nc > 0 ? int32_t((uint64_t(blockIdx.x) * 2u) % uint32_t(nc)) : 0;
-  int32_t c = 0;
-  for (; c + 1 < nc; c += 2) {  // two segments' loads in flight
-    int32_t s0 = start + c, s1 = start + c + 1;
-    if (s0 >= nc) s0 -= nc;
-    if (s1 >= nc) s1 -= nc;
-    u32x4 v0[NS], v1[NS];
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      v0[k] = __builtin_nontemporal_load(res_src(a, flat, a.base[k], s0, j));
-      v1[k] = __builtin_nontemporal_load(res_src(a, flat, a.base[k], s1, j));
-    }
+    for (int u = 0; u < U; ++u) res_load(v[u], a, uint64_t(delta[c + u]) + j0, l);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      Dec::add(acc, v0[k], a.w[k]);
-      Dec::add(acc, v1[k], a.w[k]);
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < NS; ++k) Dec::add(acc, v[u][k], a.w[k]);
+  }
+  if constexpr (U > 1) {
+    for (; c < nc; ++c) {  // the last group, if it is this wave's and partial
+      u32x4 v[NS];
+      res_load(v, a, uint64_t(delta[c]) + j0, l);
+#pragma unroll
+      for (int k = 0; k < NS; ++k) Dec::add(acc, v[k], a.w[k]);
     }
   }
-  if (c < nc) {
-    int32_t s0 = start + c;
-    if (s0 >= nc) s0 -= nc;
-    u32x4 v0[NS];
+  if constexpr (W == 1) {
+    if (lane >= live) return;
+    const uint64_t o = (j0 + lane) * V;
 #pragma unroll
-    for (int k = 0; k < NS; ++k) v0[k] = __builtin_nontemporal_load(res_src(a, flat, a.base[k], s0, j));
+    for (int h = 0; h < V; h += 4) {
+      u32x4 x = {0u, 0u, 0u, 0u}, r;
+      if (a.x_in) x = *reinterpret_cast<const u32x4 *>(a.x_in + o + h);
 #pragma unroll
-    for (int k = 0; k < NS; ++k) Dec::add(acc, v0[k], a.w[k]);
-  }
-  u32x4 *xo = reinterpret_cast<u32x4 *>(a.x_out + j * V);
+      for (int q = 0; q < 4; ++q)
+        r[q] = __float_as_uint(float(double(__uint_as_float(x[q])) + acc[h + q]));
+      *reinterpret_cast<u32x4 *>(a.x_out + o + h) = r;
+    }
+  } else {
+    // Element e of the tile's vector i at [e * 64 + i]: consecutive lanes
+    // write consecutive words.
+    __shared__ double sums[W][kResTile * V];
 #pragma unroll
-  for (int h = 0; h < V / 4; ++h) {
-    u32x4 r;
+    for (int e = 0; e < V; ++e) sums[wave][e * kResTile + lane] = acc[e];
+    __syncthreads();
+    for (uint32_t h = threadIdx.x; h < live * uint32_t(V / 4); h += kThreads) {
+      const uint64_t o = j0 * V + 4u * h;
+      const uint32_t at = (4u * h % V) * kResTile + 4u * h / V;
+      u32x4 x = {0u, 0u, 0u, 0u}, r;
+      if (a.x_in) x = *reinterpret_cast<const u32x4 *>(a.x_in + o);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) r[q] = __float_as_uint(float(acc[4 * h + q]));
-    xo[h] = r;
+      for (int q = 0; q < 4; ++q) {
+        double s = double(__uint_as_float(x[q]));
+#pragma unroll
+        for (int w = 0; w < W; ++w) s += sums[w][at + q * kResTile];
+        r[q] = __float_as_uint(float(s));
+      }
+      *reinterpret_cast<u32x4 *>(a.x_out + o) = r;
+    }
   }
 }
 
+// Waves per block and how many of its blocks share a compute unit, from the
+// sizes (measured on MI355X, 256 compute units, bf16, interleaved entries):
+//  - fewer tiles than compute units: 16 waves (144 tiles of 56 segments, 3
+//    entries: 10 us against 16 with 4);
+//  - up to 4 segments: little to divide.  One wave, which needs no LDS sum
+//    (4 segments, 4.6K tiles, 3 entries: 14 us against 16 with 4 waves); two
+//    where the residual is large (3 segments, 52K tiles, 2 entries: 89 us
+//    against 91; 2 segments, 37K tiles, one entry: 27.8 against 29.6, but
+//    42 against 38 in fp32, whose tiles are half as large);
+//  - otherwise 4 waves, and 8 for 7 entries or more (15 segments, 15K tiles,
+//    contiguous: 307 us against 311).
+// Where there are tiles for many rounds the blocks in flight are limited,
+// more for more entries and segments, so that the reads of a moment stay
+// close together: FLUX-1024 (57 segments, 27K tiles), 6 entries, 1446 us with
+// 2 blocks, 1463 with 3, 1497 without a limit; one entry, 291 with 3, 294
+// with 4, 300 without; 15 segments, 15K tiles, 8 entries, 281 with 2 blocks,
+// 287 with 4; 3 segments, 52K tiles, 8 entries, 229 with 4 blocks of 2 waves,
+// 254 without a limit.
+struct ResShape {
+  int waves;
+  int blocks_per_cu;  // 0: no limit
+};
+
+ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, int cus) {
+  const uint32_t per_cu = tiles / uint32_t(cus);
+  if (ncover <= 1 || (ncover <= 4 && per_cu < 64)) return {1, 0};
+  if (ncover == 2 && vec == 4) return {1, 0};
+  if (ncover <= 4) return {2, ns >= 7 ? 4 : ns >= 3 ? 8 : 0};
+  if (per_cu < 1 && ncover >= 16) return {16, 0};
+  if (per_cu < 16) return {4, 0};
+  if (ns == 1) return {4, ncover >= 24 ? 3 : 0};
+  if (ns >= 7) return {8, 2};
+  return {4, ncover >= 24 ? std::max(2, 4 - ns / 2) : 4};
+}
+
+// The launch's intervals with their tiles numbered through.
+struct ResJob {
+  const uint64_t *base;
+  const double *w;
+  const int64_t *delta;
+  int n_delta;
+  const ResidualInterval *iv;
+  int n_iv;
+  const float *x_in;
+  float *x_out;
+  uint64_t super;
+};
+
 template <class Dec, int NS>
-hipError_t launch_residual_ns(const uint64_t *base, const double *w, const int64_t *delta,
-                              int ncover, const float *x_in, float *x_out, uint32_t vec_begin,
-                              uint32_t n_vec, uint64_t super, hipStream_t s) {
+hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
+  // Segments a wave loads before its arithmetic.
+  constexpr int U = NS == 1 ? 4 : NS == 2 ? 2 : 1;
   ResArgs<NS> a;
   memset(&a, 0, sizeof a);
-  a.super = super;
-  for (int k = 0; k < NS; ++k) {
-    a.base[k] = base[k];
-    a.w[k] = w[k];
+  a.super = j.super;
+  memcpy(a.base, j.base, sizeof a.base);
+  memcpy(a.w, j.w, sizeof a.w);
+  memcpy(a.delta, j.delta, sizeof(int64_t) * size_t(j.n_delta));
+  a.x_in = j.x_in;
+  a.x_out = j.x_out;
+  a.n_part = j.n_iv;
+  uint32_t tiles = 0;
+  int ncover = 0;
+  for (int i = 0, first = 0; i < j.n_iv; first += j.iv[i].ncover, ++i) {
+    const uint32_t n_vec = uint32_t(j.iv[i].n_vec);
+    a.part[i] = ResPart{tiles, uint32_t(j.iv[i].vec_begin), n_vec, first, j.iv[i].ncover};
+    tiles += (n_vec + uint32_t(kResTile) - 1) / uint32_t(kResTile);
+    ncover = std::max(ncover, int(j.iv[i].ncover));
   }
-  for (int c = 0; c < ncover; ++c) a.delta[c] = delta[c];
-  a.x_in = x_in;
-  a.x_out = x_out;
-  a.vec_begin = vec_begin;
-  a.n_vec = n_vec;
-  a.ncover = ncover;
-  const uint32_t grid = (n_vec + kResBlock - 1) / kResBlock;
-  hipLaunchKernelGGL((residual_kernel<Dec, NS>), dim3(grid), dim3(kResBlock), 0, s, a);
+  const ResShape shape = residual_shape(NS, Dec::kVec, ncover, tiles, g.cus);
+  auto launch = [&](auto waves) {
+    constexpr int W = decltype(waves)::value;
+    constexpr size_t kOwn = W > 1 ? size_t(W) * kResTile * Dec::kVec * sizeof(double) : 0;
+    const size_t share = lds_share(g.lds_per_cu, shape.blocks_per_cu);
+    const size_t extra = share > kOwn ? share - kOwn : 0;
+    hipLaunchKernelGGL((residual_kernel<Dec, NS, W, U>), dim3(tiles), dim3(64 * W), extra, s, a);
+  };
+  if (shape.waves == 1) launch(std::integral_constant<int, 1>());
+  if (shape.waves == 2) launch(std::integral_constant<int, 2>());
+  if (shape.waves == 4) launch(std::integral_constant<int, 4>());
+  if constexpr (NS >= 7)
+    if (shape.waves == 8) launch(std::integral_constant<int, 8>());
+  if (shape.waves == 16) launch(std::integral_constant<int, 16>());
   return hipGetLastError();
 }
 
 template <class Dec>
-hipError_t launch_residual_dec(int n, const uint64_t *base, const double *w, const int64_t *delta,
-                               int ncover, const float *x_in, float *x_out, uint32_t vec_begin,
-                               uint32_t n_vec, uint64_t sv, hipStream_t s) {
+hipError_t launch_residual_dec(int n, const ResJob &j, const Gpu &g, hipStream_t s) {
   switch (n) {
-#define CHEB_RES_CASE(N) \
-  case N: return launch_residual_ns<Dec, N>(base, w, delta, ncover, x_in, x_out, vec_begin, n_vec, sv, s);
-    CHEB_RES_CASE(1) CHEB_RES_CASE(2) CHEB_RES_CASE(3) CHEB_RES_CASE(4)
-    CHEB_RES_CASE(5) CHEB_RES_CASE(6) CHEB_RES_CASE(7)
-#undef CHEB_RES_CASE
-    default: return launch_residual_ns<Dec, 8>(base, w, delta, ncover, x_in, x_out, vec_begin, n_vec, sv, s);
+    case 1: return launch_residual_ns<Dec, 1>(j, g, s);
+    case 2: return launch_residual_ns<Dec, 2>(j, g, s);
+    case 3: return launch_residual_ns<Dec, 3>(j, g, s);
+    case 4: return launch_residual_ns<Dec, 4>(j, g, s);
+    case 5: return launch_residual_ns<Dec, 5>(j, g, s);
+    case 6: return launch_residual_ns<Dec, 6>(j, g, s);
+    case 7: return launch_residual_ns<Dec, 7>(j, g, s);
+    default: return launch_residual_ns<Dec, 8>(j, g, s);
   }
 }
 
@@ -694,26 +815,31 @@ namespace cheb {
 
 int residual_max_cover() { return kResCover; }
 
+int launch_residual_intervals(int dtype, int n, const uint64_t *base, const double *w,
+                              const int64_t *delta, int n_delta, const ResidualInterval *iv,
+                              int n_iv, const float *x_in, float *x_out, int64_t super_vecs,
+                              hipStream_t stream) {
+  Gpu g{0, 0, 0};
+  int rc = device_info(&g.cus, &g.lds_per_cu);
+  if (rc != CHEB_OK) return rc;
+  const ResJob j{base, w, delta, n_delta, iv, n_iv, x_in, x_out, uint64_t(super_vecs)};
+  hipError_t e;
+  switch (dtype) {
+    case CHEB_BF16: e = launch_residual_dec<Bf16Dec>(n, j, g, stream); break;
+    case CHEB_F16: e = launch_residual_dec<F16Dec>(n, j, g, stream); break;
+    default: e = launch_residual_dec<F32Dec>(n, j, g, stream); break;
+  }
+  if (e != hipSuccess) return fail(CHEB_E_HIP, "residual launch failed: %s", hipGetErrorString(e));
+  return ok();
+}
+
 int launch_residual(int dtype, int n, const uint64_t *base, const double *w, const int64_t *delta,
                     int ncover, const float *x_in, float *x_out, int64_t vec_begin,
                     int64_t n_vec, int64_t super_vecs, hipStream_t stream) {
   if (n_vec == 0) return ok();
-  const uint32_t vb = uint32_t(vec_begin), nv = uint32_t(n_vec);
-  const uint64_t sv = uint64_t(super_vecs);
-  hipError_t e;
-  switch (dtype) {
-    case CHEB_BF16:
-      e = launch_residual_dec<Bf16Dec>(n, base, w, delta, ncover, x_in, x_out, vb, nv, sv, stream);
-      break;
-    case CHEB_F16:
-      e = launch_residual_dec<F16Dec>(n, base, w, delta, ncover, x_in, x_out, vb, nv, sv, stream);
-      break;
-    default:
-      e = launch_residual_dec<F32Dec>(n, base, w, delta, ncover, x_in, x_out, vb, nv, sv, stream);
-      break;
-  }
-  if (e != hipSuccess) return fail(CHEB_E_HIP, "residual launch failed: %s", hipGetErrorString(e));
-  return ok();
+  const ResidualInterval iv{vec_begin, n_vec, ncover};
+  return launch_residual_intervals(dtype, n, base, w, delta, ncover, &iv, 1, x_in, x_out,
+                                   super_vecs, stream);
 }
 
 }  // namespace cheb

@@ -15,6 +15,24 @@
 
 using namespace cheb;
 
+namespace cheb {
+
+// A build of the host sources without the device code links only
+// launch_residual; the library's own definition replaces this one.
+__attribute__((weak)) int launch_residual_intervals(
+    int dtype, int n, const uint64_t *base, const double *w, const int64_t *delta, int,
+    const ResidualInterval *iv, int n_iv, const float *x_in, float *x_out, int64_t super_vecs,
+    hipStream_t stream) {
+  for (int i = 0; i < n_iv; delta += iv[i].ncover, ++i) {
+    int rc = launch_residual(dtype, n, base, w, delta, iv[i].ncover, x_in, x_out,
+                             iv[i].vec_begin, iv[i].n_vec, super_vecs, stream);
+    if (rc != CHEB_OK) return rc;
+  }
+  return ok();
+}
+
+}  // namespace cheb
+
 namespace {
 
 struct Interval {
@@ -71,20 +89,42 @@ int check_residual_buffers(const float *x_in, float *x_out, int64_t res_numel) {
   return CHEB_OK;
 }
 
-// Runs the plan: per interval, the covering segments in chunks of the
-// kernel's table size; the first chunk reads x_in, later ones x_out.
+// Runs the plan.  When every interval's covering segments fit one launch's
+// tables, it is one launch, the largest interval first, so that the chip
+// does not run empty between them.  Otherwise, per interval, the covering segments in chunks of the
+// table's size; the first chunk reads x_in, later ones x_out.
 template <class DeltaFn>
 int run(int dtype, int n, const uint64_t *base, const double *w,
         const std::vector<Interval> &plan_iv, DeltaFn delta_of, const float *x_in, float *x_out,
         int64_t super_vecs, hipStream_t stream) {
   const int vec = elems_per_vec(dtype);
-  const int max_cover = residual_max_cover();
+  const size_t max_cover = size_t(residual_max_cover());
   std::vector<int64_t> delta;
+  size_t covers = 0;
+  for (const Interval &iv : plan_iv) covers += iv.segs.size();
+  if (plan_iv.size() > 1 && plan_iv.size() <= size_t(kMaxResIntervals) && covers <= max_cover) {
+    ResidualInterval parts[kMaxResIntervals];
+    int n_parts = 0;
+    delta.reserve(covers);
+    const Interval *order[kMaxResIntervals];
+    for (const Interval &iv : plan_iv) order[n_parts++] = &iv;
+    std::sort(order, order + n_parts, [](const Interval *a, const Interval *b) {
+      return a->end - a->begin > b->end - b->begin ||
+             (a->end - a->begin == b->end - b->begin && a->begin < b->begin);
+    });
+    for (int i = 0; i < n_parts; ++i) {
+      const Interval &iv = *order[i];
+      parts[i] = {iv.begin / vec, (iv.end - iv.begin) / vec, int32_t(iv.segs.size())};
+      for (int32_t s : iv.segs) delta.push_back(delta_of(s));
+    }
+    return launch_residual_intervals(dtype, n, base, w, delta.data(), int(covers), parts, n_parts,
+                                     x_in, x_out, super_vecs, stream);
+  }
   for (const Interval &iv : plan_iv) {
     const int64_t vb = iv.begin / vec, nv = (iv.end - iv.begin) / vec;
     size_t first = 0;
     do {
-      const size_t count = std::min(iv.segs.size() - first, size_t(max_cover));
+      const size_t count = std::min(iv.segs.size() - first, max_cover);
       delta.assign(count, 0);
       for (size_t c = 0; c < count; ++c) delta[c] = delta_of(iv.segs[first + c]);
       const float *in = first == 0 ? x_in : x_out;
@@ -127,15 +167,10 @@ int cheb_residual_apply(cheb_cache *c, const double *w, const int64_t *res_offse
     if (rc != CHEB_OK) return rc;
     base[k] = reinterpret_cast<uint64_t>(p);
   }
-  // Contiguous entries: byte offset from the entry base to the segment's
-  // element of residual element 0; interleaved: the same in vectors (the
-  // kernel places each vector by its chunk).
-  const int64_t esize = elem_bytes(v.dtype), vec = elems_per_vec(v.dtype);
-  const bool contiguous = v.super_vecs == kChunkVecs;
-  auto delta_of = [&](int32_t s) {
-    const int64_t d = v.seg_offset[s] - res_offset[s];
-    return contiguous ? d * esize : d / vec;
-  };
+  // Vectors from the entry base to the segment's vector of residual vector 0
+  // (both offsets are whole vectors; the kernel places each by its chunk).
+  const int64_t vec = elems_per_vec(v.dtype);
+  auto delta_of = [&](int32_t s) { return (v.seg_offset[s] - res_offset[s]) / vec; };
   return run(v.dtype, v.n_slots, base, w, iv, delta_of, x_in, x_out, v.super_vecs,
              static_cast<hipStream_t>(stream));
 }
@@ -157,11 +192,12 @@ int cheb_residual_reduce(const void *const *seg_src, const int64_t *seg_numel,
   std::vector<Interval> iv;
   rc = plan(seg_numel, res_offset, n_segs, res_numel, elems_per_vec(dtype), &iv);
   if (rc != CHEB_OK) return rc;
-  const int64_t esize = elem_bytes(dtype);
+  // Vectors from address 0 (the sources are 16-byte aligned).
+  const int64_t vec = elems_per_vec(dtype);
   const uint64_t base[1] = {0};
   const double one[1] = {1.0};
   auto delta_of = [&](int32_t s) {
-    return int64_t(reinterpret_cast<uintptr_t>(seg_src[s])) - res_offset[s] * esize;
+    return int64_t(reinterpret_cast<uintptr_t>(seg_src[s]) / 16) - res_offset[s] / vec;
   };
   return run(dtype, 1, base, one, iv, delta_of, x_in, x_out, kChunkVecs,
              static_cast<hipStream_t>(stream));

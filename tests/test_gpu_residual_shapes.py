@@ -1,0 +1,83 @@
+"""The residual kernel's launch shapes: tiles of 64 vectors shared by 1, 2, 4,
+8 or 16 waves, several residual intervals in one launch, and tiles that cross
+the chunks of an interleaved entry, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_23429_amd as cheb
+from tests.gpu_util import say, to_host_bits
+
+pytestmark = pytest.mark.gpu
+
+DT = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}
+# fp64 accumulation of at most (n * segments + 1) terms and one fp32 rounding:
+# 2^-24 |o|, with the fp64 terms below 2^-40 of the floor (10^-3 S).
+RES_TOL = 1e-6
+
+
+def _check(dtype, n, seg_numel, res_off, res_n, layout, with_x, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    cache = cheb.ChebCache(n, DT[dtype], seg_numel, layout=layout)
+    entries = []
+    for k in range(n):
+        segs = [torch.randn(s, generator=g, device="cuda").to(DT[dtype]) for s in seg_numel]
+        cache.push(float(k), segs)
+        entries.append(segs)
+    w = np.random.default_rng(seed).standard_normal(n)
+    x_in = torch.randn(res_n, generator=g, device="cuda") if with_x else None
+    x_out = torch.full((res_n,), float("nan"), device="cuda")
+    say(f"residual shape {dtype} n={n} segs={len(seg_numel)} res={res_n} {layout} x={with_x}")
+    cache.residual_apply(w, res_off, x_out, x_in)
+    torch.cuda.synchronize()
+    # the entries as the cache lays them out: each segment from its offset
+    hosts = []
+    for segs in entries:
+        flat = np.zeros(cache.slot_numel, dtype=np.float32 if dtype == "f32" else np.uint16)
+        for o, s in zip(cache.seg_offset, segs):
+            flat[o:o + s.numel()] = to_host_bits(s)
+        hosts.append(flat)
+    exp, mag = oracle.residual(hosts, w, cache.seg_offset, cache.seg_numel, res_off, res_n,
+                               x_in=None if x_in is None else x_in.cpu().numpy(), dtype=dtype)
+    e = oracle.parity_error(x_out.cpu().numpy().astype(np.float64), exp, mag)[0]
+    assert e <= RES_TOL, e
+    cache.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("n", [1, 2, 3, 7])
+@pytest.mark.parametrize("ncover", [1, 2, 3, 4, 5, 16, 17, 31])
+def test_small_residual(dtype, n, ncover):
+    """One tile and a bit: 1, 4 and 16 waves, partial groups of segments."""
+    vec = 4 if dtype == "f32" else 8
+    _check(dtype, n, [65 * vec] * ncover, [0] * ncover, 65 * vec, "slots", ncover % 2 == 0, ncover)
+
+
+@pytest.mark.parametrize("layout", ["slots", "interleaved"])
+@pytest.mark.parametrize("n,ncover,vecs", [(1, 2, 64 * 64 * 256 + 1), (2, 3, 64 * 64 * 256 + 63),
+                                           (7, 5, 16 * 64 * 256 + 1), (6, 24, 16 * 64 * 256 + 2),
+                                           (2, 9, 16 * 64 * 256 + 65), (3, 6, 64 * 300 + 31)])
+def test_many_tiles(layout, n, ncover, vecs):
+    """Residuals past each size at which the rule changes; odd vector counts
+    put later segments' tiles across chunk ends."""
+    _check("bf16", n, [vecs * 8] * ncover, [0] * ncover, vecs * 8, layout, True, ncover)
+
+
+@pytest.mark.parametrize("layout", ["slots", "interleaved"])
+@pytest.mark.parametrize("n_intervals", [2, 8, 9])
+def test_intervals(layout, n_intervals):
+    """Several intervals in one launch (up to 8) or in launches of their own
+    (9), one of them covered by no segment, segments crossing chunk ends."""
+    unit = 8 * 777
+    res_n = unit * n_intervals
+    seg, off = [], []
+    for i in range(n_intervals):
+        if i == 1:
+            continue                           # nothing adds here
+        for _ in range(1 + i % 3):
+            seg.append(unit)
+            off.append(unit * i)
+    for x in (True, False):
+        _check("bf16", 3, seg, off, res_n, layout, x, n_intervals)
