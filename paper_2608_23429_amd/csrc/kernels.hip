@@ -202,17 +202,62 @@ struct F32Op {
   }
 };
 
-// ---- the streaming kernel -------------------------------------------------
+// ---- the streaming kernels -------------------------------------------------
 //
-// The vector range [0, n_vec) is cut into tiles of BLK * U vectors.  A block
-// takes tiles blockIdx.x, blockIdx.x + gridDim.x, ... (one tile per block
-// when the grid covers the range, a persistent loop otherwise).  In a tile,
-// lane t handles vectors t, t + BLK, ..., so every load instruction of a
-// wave reads 64 consecutive 16-byte vectors (1 KiB).  A scheduling barrier
-// keeps all NS x U loads of a thread ahead of its arithmetic, so each wave
-// has its whole working set in flight before it waits.  With NO > 1 the same
-// loaded history feeds NO weight rows and NO outputs: every skipped step
-// between two full steps is predicted in one pass over the history.
+// The default: one-wave blocks, each a tile of 64 vectors, so every load or
+// store instruction covers 1 KiB contiguous.  The tile's place in the history
+// is uniform (a chunk holds 32 tiles, none crosses one), so it is scalar
+// arithmetic and a load takes a scalar base and the lane's offset.  A
+// scheduling barrier keeps all NS loads ahead of the arithmetic.  With NO > 1
+// the loaded history feeds NO weight rows and NO outputs: every skipped step
+// between two full steps is predicted in one pass.  Bound by HBM: NS KiB read
+// and NO KiB written per block and next to no arithmetic; how many blocks
+// share a compute unit (auto_waves) decides how well reads and writes mix.
+// The last block takes the vectors past the last whole tile and the ragged
+// tail, which only contiguous sources have.
+template <class Op, int NS, int NO, bool NT>
+__global__ __launch_bounds__(64) void stream_kernel(Hist<NS, NO, typename Op::W> h, uint32_t n_vec,
+                                                    Tail tail) {
+  const uint32_t first = blockIdx.x * 64u;
+  const uint32_t lane = threadIdx.x;
+  const uint64_t at = lane_vec(first, h.super);
+  if (first + 64u <= n_vec) {
+    u32x4 v[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) v[k] = load16<NT>(h.p[k] + at + lane);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < NO; ++m)
+      store16<NT>(h.o[m] + first + lane, Op::template vec<NS>(v, h.w[m]));
+    return;
+  }
+  if (first + lane < n_vec) {
+    u32x4 v[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) v[k] = load16<NT>(h.p[k] + at + lane);
+#pragma unroll
+    for (int m = 0; m < NO; ++m)
+      store16<NT>(h.o[m] + first + lane, Op::template vec<NS>(v, h.w[m]));
+  }
+  if (lane < tail.count) {
+    using E = typename Op::E;
+    const E *p[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) p[k] = reinterpret_cast<const E *>(h.p[k]);
+    const uint64_t i = tail.first + lane;
+#pragma unroll
+    for (int m = 0; m < NO; ++m)
+      reinterpret_cast<E *>(h.o[m])[i] = Op::template scalar<NS>(p, h.w[m], i);
+  }
+}
+
+// The other launch shapes of the tuning interface.  The vector range
+// [0, n_vec) is cut into tiles of BLK * U vectors.  A block takes tiles
+// blockIdx.x, blockIdx.x + gridDim.x, ... (one tile per block when the grid
+// covers the range, a persistent loop otherwise).  In a tile, lane t handles
+// vectors t, t + BLK, ..., so every load instruction of a wave reads 64
+// consecutive 16-byte vectors (1 KiB), all NS x U of them ahead of its
+// arithmetic.
 template <class Op, int NS, int NO, int BLK, int U, bool NT>
 __global__ __launch_bounds__(BLK) void combine_kernel(Hist<NS, NO, typename Op::W> h,
                                                       uint32_t n_vec, uint32_t n_tiles,
@@ -276,23 +321,45 @@ struct Gpu {
   int waves;       // occupancy cap in waves per compute unit, 0: none
 };
 
-// Waves per compute unit the prediction streams best with, from the history
-// size NS and the number of outputs NO.  Measured on MI355X (FLUX- and
-// DiT-sized bf16 streams): the mix of NS reads and the output's writes runs
-// fastest with about 44 KiB of loads in flight per compute unit for one
-// output (NS x 1 KiB per 64-lane wave: 7 waves for NS = 6, 9 for NS = 5)
-// and about 36 KiB for several (6 and 7); more waves flood the memory queues
-// and slow the writes.  Below 6 waves the latency is no longer covered and
-// the rate falls steeply, hence the floor.  Two entries or fewer stream as
-// well at full occupancy: no cap.
+// One-wave blocks that share a compute unit, from the history size, the
+// number of outputs, the layout and the work (0: no limit).  Too few leave the
+// memory latency uncovered, too many flood the memory queues and slow the
+// writes.  Measured on MI355X, bf16, entries of 0.1 to 1.6 GB, within 3% of
+// the best of 5 to 25 blocks and none:
+//  - one output: about 40 KiB of loads in flight from interleaved entries, 45
+//    to 48 from contiguous ones (6 interleaved entries of 1.6 GB: 1627 us with
+//    7, 1642 with 6, over 1670 with 8; 5 contiguous ones: 1417 us with 9, 1447
+//    with 10); up to two entries stream as well without a limit;
+//  - several outputs: about 60 KiB of loads and stores (2 entries, 5 outputs
+//    of 264 MB: 291 us with 9, 299 with 12, 319 without a limit), and not
+//    below 6 to 8;
+//  - a call of under 512 KiB a compute unit is over before the queues fill
+//    and wants twice as many (6 entries of 9 MB: 11.4 us with 16, 12.6 with
+//    7).
+int stream_blocks(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
+  static constexpr int kOne[2][CHEB_MAX_SLOTS + 1] = {{0, 0, 0, 16, 11, 9, 8, 7, 6},
+                                                      {0, 0, 0, 14, 9, 8, 7, 6, 5}};
+  const int sum = ns + no;
+  int blocks = kOne[interleaved][ns];
+  if (no > 1) {
+    const int least = sum >= 12 ? 6 : sum <= 9 && !interleaved ? 8 : 7;
+    blocks = std::max(least, (60 + sum / 2) / sum);
+  }
+  const uint64_t kib_per_cu = uint64_t(n_vec / 64u) * uint64_t(sum) / uint64_t(cus);
+  return kib_per_cu < 512 ? 2 * blocks : blocks;
+}
+
+// Waves per compute unit of the other launch shapes, whose loops and larger
+// blocks came out best at 44 KiB of loads in flight (one output) and 36
+// (several).
 int auto_waves(int ns, int no) {
   if (ns <= 2) return 0;
   const int kib = no == 1 ? 44 : 36;
   return std::max(6, (kib + ns / 2) / ns);
 }
 
-// LDS bytes of one block when `blocks` of them are to share a compute unit:
-// an equal share rounded down to the 1280-byte unit LDS is handed out in on
+// Dynamic LDS a block reserves, and never touches, when `blocks` of them are
+// to share a compute unit: an equal share rounded down to the 1280-byte unit LDS is handed out in on
 // gfx950 (a size in between takes the next unit, and one block fewer fits).
 // A share past the 64 KiB a block may have is cut to that, if as many blocks
 // still fit and no more.  Zero when there is no limit or none is possible.
@@ -304,8 +371,8 @@ size_t lds_share(int lds_per_cu, int blocks) {
   return lds_per_cu / kMost == blocks ? size_t(kMost) : 0;
 }
 
-// Dynamic LDS a block reserves, and never touches, so that about `waves`
-// waves of the kernel share a compute unit (the LDS is what runs out): an
+// The same for the other launch shapes, so that about `waves` waves of the
+// kernel share a compute unit (the LDS is what runs out): an
 // equal share of the compute unit's LDS, rounded down to 512 bytes.  Zero
 // when there is no cap, when the cap is at the hardware's own limit, or when
 // one block would need more than the default 64 KiB of dynamic LDS.
@@ -331,6 +398,18 @@ hipError_t launch_shape(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, T
   return hipGetLastError();
 }
 
+// The default launch shape: one-wave blocks, as many of them on a compute
+// unit as dev.waves says.
+template <class Op, int NS, int NO, bool NT>
+hipError_t launch_stream(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, Tail tail,
+                         const Gpu &g, hipStream_t s) {
+  const uint32_t grid = n_vec / 64u + (n_vec % 64u != 0 || tail.count != 0 ? 1u : 0u);
+  hipLaunchKernelGGL((stream_kernel<Op, NS, NO, NT>), dim3(grid), dim3(64),
+                     g.waves > 2 && g.waves < 32 ? lds_share(g.lds_per_cu, g.waves) : 0, s, h, n_vec,
+                     tail);
+  return hipGetLastError();
+}
+
 // Single output: every launch shape of the tuning interface.
 template <class Op, int NS, bool NT>
 hipError_t launch_one(const Hist<NS, 1, typename Op::W> &h, uint32_t n_vec, Tail tail,
@@ -339,6 +418,7 @@ hipError_t launch_one(const Hist<NS, 1, typename Op::W> &h, uint32_t n_vec, Tail
   // A problem too small to give every compute unit a few 1024-thread blocks
   // runs with 256-thread blocks instead (four times as many blocks).
   const bool small = uint64_t(n_vec) < uint64_t(4 * 1024) * uint64_t(dev.cus);
+  if (b == 64 && g == 0) return launch_stream<Op, NS, 1, NT>(h, n_vec, tail, dev, s);
   if (b == 64) return launch_shape<Op, NS, 1, 64, 1, NT>(h, n_vec, tail, g, dev, s);
   if (b == 1024 && small) return launch_shape<Op, NS, 1, 256, 1, NT>(h, n_vec, tail, g, dev, s);
   if (b == 1024) return launch_shape<Op, NS, 1, 1024, 1, NT>(h, n_vec, tail, g, dev, s);
@@ -352,15 +432,14 @@ hipError_t launch_one(const Hist<NS, 1, typename Op::W> &h, uint32_t n_vec, Tail
 }
 
 // Several outputs: one vector per lane, a grid covering the range, 64-lane
-// blocks (under the occupancy cap) or 1024-lane blocks for any other
-// configured block, and the non-temporal hint as configured; this keeps the
+// blocks or 1024-lane blocks for any other configured block, and the non-temporal hint as configured; this keeps the
 // number of kernel instances bounded.
 template <class Op, int NS, int NO>
 hipError_t launch_many(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, Tail tail,
                        const cheb_launch_config &cfg, const Gpu &dev, hipStream_t s) {
   if (cfg.block == 64)
-    return cfg.nontemporal ? launch_shape<Op, NS, NO, 64, 1, true>(h, n_vec, tail, 0, dev, s)
-                           : launch_shape<Op, NS, NO, 64, 1, false>(h, n_vec, tail, 0, dev, s);
+    return cfg.nontemporal ? launch_stream<Op, NS, NO, true>(h, n_vec, tail, dev, s)
+                           : launch_stream<Op, NS, NO, false>(h, n_vec, tail, dev, s);
   return cfg.nontemporal ? launch_shape<Op, NS, NO, 1024, 1, true>(h, n_vec, tail, 0, dev, s)
                          : launch_shape<Op, NS, NO, 1024, 1, false>(h, n_vec, tail, 0, dev, s);
 }
@@ -371,7 +450,6 @@ hipError_t launch_ns_no(const void *const *src, const double *w, void *const *ou
                         const Gpu &dev0, hipStream_t s) {
   constexpr int kVec = 16 / int(sizeof(typename Op::E));
   Gpu dev = dev0;
-  dev.waves = cfg.waves_per_cu == 0 ? auto_waves(NS, NO) : std::max(0, cfg.waves_per_cu);
   Hist<NS, NO, typename Op::W> h;
   h.super = uint64_t(super_vecs);
   for (int k = 0; k < NS; ++k) h.p[k] = static_cast<const u32x4 *>(src[k]);
@@ -380,6 +458,12 @@ hipError_t launch_ns_no(const void *const *src, const double *w, void *const *ou
     for (int k = 0; k < NS; ++k) h.w[m][k] = static_cast<typename Op::W>(w[m * NS + k]);
   }
   const uint32_t n_vec = uint32_t(numel / kVec);
+  if (cfg.waves_per_cu != 0)
+    dev.waves = std::max(0, cfg.waves_per_cu);
+  else if (cfg.block == 64 && cfg.blocks_per_cu == 0)
+    dev.waves = stream_blocks(NS, NO, super_vecs != kChunkVecs, n_vec, dev.cus);
+  else
+    dev.waves = auto_waves(NS, NO);
   Tail tail{uint32_t(numel % kVec), uint64_t(numel / kVec) * kVec};
   if constexpr (NO == 1) {
     return cfg.nontemporal ? launch_one<Op, NS, true>(h, n_vec, tail, cfg, dev, s)
