@@ -44,8 +44,15 @@ def cheb_dtype(dtype: torch.dtype) -> int:
         raise ChebError(_binding.CHEB_E_DTYPE, f"unsupported dtype {dtype}") from None
 
 
+# The current stream's handle without a Stream object around it (0.2 us for
+# 1.5), where torch has the call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
@@ -57,6 +64,12 @@ def _check_device_tensor(t: torch.Tensor, what: str):
         raise ChebError(_binding.CHEB_E_INVAL, f"{what} must be contiguous")
 
 
+def _plain(t, dtype: torch.dtype, numel: int) -> bool:
+    """Whether t is a contiguous GPU tensor of that type and size."""
+    return (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype
+            and t.numel() == numel and t.is_contiguous())
+
+
 def combine(srcs: Sequence[torch.Tensor], w, out: torch.Tensor,
             stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """out = sum_k w[k] * srcs[k] (elementwise, one launch of cheb_combine)."""
@@ -64,11 +77,12 @@ def combine(srcs: Sequence[torch.Tensor], w, out: torch.Tensor,
         raise ChebError(_binding.CHEB_E_INVAL, "no sources")
     dt = cheb_dtype(out.dtype)
     _check_device_tensor(out, "out")
+    dtype, numel = out.dtype, out.numel()
     for i, s in enumerate(srcs):
-        _check_device_tensor(s, f"srcs[{i}]")
-        if s.dtype != out.dtype or s.numel() != out.numel():
+        if not _plain(s, dtype, numel):
+            _check_device_tensor(s, f"srcs[{i}]")
             raise ChebError(_binding.CHEB_E_MISMATCH, f"srcs[{i}] differs from out in dtype or size")
-    cheb_combine([s.data_ptr() for s in srcs], w, out.data_ptr(), out.numel(), dt,
+    cheb_combine([s.data_ptr() for s in srcs], w, out.data_ptr(), numel, dt,
                  _stream_handle(stream))
     return out
 
@@ -80,9 +94,10 @@ def combine_multi(srcs: Sequence[torch.Tensor], w, outs: Sequence[torch.Tensor],
     if len(srcs) == 0 or len(outs) == 0:
         raise ChebError(_binding.CHEB_E_INVAL, "no sources or no outputs")
     dt = cheb_dtype(outs[0].dtype)
+    dtype, numel = outs[0].dtype, outs[0].numel()
     for i, t in enumerate(list(srcs) + list(outs)):
-        _check_device_tensor(t, f"tensor {i}")
-        if t.dtype != outs[0].dtype or t.numel() != outs[0].numel():
+        if not _plain(t, dtype, numel):
+            _check_device_tensor(t, f"tensor {i}")
             raise ChebError(_binding.CHEB_E_MISMATCH, f"tensor {i} differs in dtype or size")
     cheb_combine_multi([s.data_ptr() for s in srcs], w, [o.data_ptr() for o in outs],
                        outs[0].numel(), dt, _stream_handle(stream))
@@ -152,18 +167,28 @@ class ChebTable:
             pass
 
 
+def _segment_args(segments: Sequence[torch.Tensor]):
+    """(addresses, sizes, storage type) of one step's module outputs."""
+    dtype = segments[0].dtype
+    dt = cheb_dtype(dtype)
+    ptrs, sizes = [], []
+    for i, t in enumerate(segments):
+        if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype
+                and t.is_contiguous()):
+            _check_device_tensor(t, f"segments[{i}]")
+            raise ChebError(_binding.CHEB_E_MISMATCH, "segments differ in dtype")
+        ptrs.append(t.data_ptr())
+        sizes.append(t.numel())
+    return ptrs, sizes, dt
+
+
 def residual_reduce(segments: Sequence[torch.Tensor], res_offset, x_out: torch.Tensor,
                     x_in: Optional[torch.Tensor] = None,
                     stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """x_out = x_in + the mapped sum of one step's module outputs."""
-    dt = cheb_dtype(segments[0].dtype)
-    for i, t in enumerate(segments):
-        _check_device_tensor(t, f"segments[{i}]")
-        if t.dtype != segments[0].dtype:
-            raise ChebError(_binding.CHEB_E_MISMATCH, "segments differ in dtype")
+    ptrs, sizes, dt = _segment_args(segments)
     _check_device_tensor(x_out, "x_out")
-    cheb_residual_reduce([t.data_ptr() for t in segments], [t.numel() for t in segments],
-                         res_offset, dt, None if x_in is None else x_in.data_ptr(),
+    cheb_residual_reduce(ptrs, sizes, res_offset, dt, None if x_in is None else x_in.data_ptr(),
                          x_out.data_ptr(), x_out.numel(), _stream_handle(stream))
     return x_out
 
@@ -181,9 +206,11 @@ class ResidualHistory:
 
     def push(self, t: float, segments: Sequence[torch.Tensor],
              stream: Optional[torch.cuda.Stream] = None):
-        slot = self.cache.begin_push()
+        slot = cheb_cache_begin_push(self.cache.handle)
         try:
-            residual_reduce(segments, self.res_offset, slot[:self.res_numel], stream=stream)
+            ptrs, sizes, dt = _segment_args(segments)
+            cheb_residual_reduce(ptrs, sizes, self.res_offset, dt, None, slot, self.res_numel,
+                                 _stream_handle(stream))
         except Exception:
             self.cache.abort_push()
             raise
@@ -201,9 +228,12 @@ class ResidualHistory:
             if x.dtype != torch.float32 or x.numel() != self.res_numel:
                 raise ChebError(_binding.CHEB_E_MISMATCH,
                                 f"{name} must be float32 with {self.res_numel} elements")
-        slot = self.cache.begin_push()
+        slot = cheb_cache_begin_push(self.cache.handle)
         try:
-            combine([x_after, x_before], [1.0, -1.0], slot[:self.res_numel], stream=stream)
+            _check_device_tensor(x_after, "srcs[0]")
+            _check_device_tensor(x_before, "srcs[1]")
+            cheb_combine([x_after.data_ptr(), x_before.data_ptr()], [1.0, -1.0], slot,
+                         self.res_numel, CHEB_F32, _stream_handle(stream))
         except Exception:
             self.cache.abort_push()
             raise
@@ -290,8 +320,7 @@ class ChebCache:
 
     def _slot_tensor(self, addr: int) -> torch.Tensor:
         start = addr - self.arena.data_ptr()
-        esz = torch.empty((), dtype=self.dtype).element_size()
-        raw = self.arena[start:start + self.slot_numel * esz]
+        raw = self.arena[start:start + self.slot_numel * self.dtype.itemsize]
         return raw.view(self.dtype)
 
     def entry(self, idx: int) -> torch.Tensor:
@@ -301,7 +330,7 @@ class ChebCache:
         addr = cheb_cache_entry(self._h, idx)
         if self.layout == "slots":
             return self._slot_tensor(addr)
-        esz = torch.empty((), dtype=self.dtype).element_size()
+        esz = self.dtype.itemsize
         start = (addr - self.arena.data_ptr()) // esz
         chunk, stride = self.chunk_elems, self.entry_stride_elems
         n_chunks = -(-self.slot_numel // chunk)
@@ -317,11 +346,15 @@ class ChebCache:
              stream: Optional[torch.cuda.Stream] = None):
         if len(segments) != len(self.seg_numel):
             raise ChebError(_binding.CHEB_E_MISMATCH, "segment count differs from the layout")
-        for i, (s, n) in enumerate(zip(segments, self.seg_numel)):
-            _check_device_tensor(s, f"segments[{i}]")
-            if s.dtype != self.dtype or s.numel() != n:
-                raise ChebError(_binding.CHEB_E_MISMATCH, f"segments[{i}] differs from the layout")
-        cheb_cache_push(self._h, t, [s.data_ptr() for s in segments], _stream_handle(stream))
+        dtype, ptrs = self.dtype, []
+        for s, n in zip(segments, self.seg_numel):
+            if not (isinstance(s, torch.Tensor) and s.is_cuda and s.dtype is dtype
+                    and s.numel() == n and s.is_contiguous()):
+                _check_device_tensor(s, f"segments[{len(ptrs)}]")
+                raise ChebError(_binding.CHEB_E_MISMATCH,
+                                f"segments[{len(ptrs)}] differs from the layout")
+            ptrs.append(s.data_ptr())
+        cheb_cache_push(self._h, t, ptrs, _stream_handle(stream))
 
     def begin_push(self) -> torch.Tensor:
         """Flat view of the slot the next entry occupies (fused push)."""

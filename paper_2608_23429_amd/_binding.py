@@ -6,6 +6,7 @@ package fails.
 """
 import ctypes
 import os
+from array import array
 
 import numpy as np
 
@@ -157,16 +158,50 @@ def _check(rc):
     return rc
 
 
+# Marshalling.  The smallest calls take a few microseconds on the device, so
+# the host side keeps to cheap conversions: addresses of arrays taken through
+# the buffer protocol (numpy's ctypes.data_as alone costs 2 us), integer
+# tables built by array.array (a ctypes array of 76 integers costs 5 us, this
+# 1.5), and results viewed, not copied, out of a buffer made for the call.
+
 def _f64(a):
     return np.ascontiguousarray(a, dtype=np.float64)
 
 
 def _dptr(a):
-    return a.ctypes.data_as(_dp)
+    """Pointer to a contiguous fp64 array; it keeps the array alive."""
+    try:
+        return ctypes.byref(ctypes.c_double.from_buffer(a))
+    except (TypeError, ValueError):            # read-only or empty
+        return a.ctypes.data_as(_dp)
 
 
 def _voidp_array(ptrs):
-    return (ctypes.c_void_p * max(1, len(ptrs)))(*[ctypes.c_void_p(int(p)) for p in ptrs])
+    """void*[] of addresses; it keeps its table alive."""
+    try:
+        return ctypes.byref(_vp.from_buffer(array("Q", ptrs)))
+    except (TypeError, ValueError, OverflowError):  # none, or not all plain addresses
+        return (_vp * max(1, len(ptrs)))(*[_vp(int(p)) for p in ptrs])
+
+
+def _i64ptr(values):
+    """int64[] of integers and its length; it keeps its table alive."""
+    if type(values) is list and values:
+        try:
+            return ctypes.byref(ctypes.c_int64.from_buffer(array("q", values))), len(values)
+        except (TypeError, OverflowError):
+            pass                               # not all plain integers: numpy converts or refuses
+    a = np.ascontiguousarray(values, dtype=np.int64).reshape(-1)
+    return a.ctypes.data_as(_i64p), a.size
+
+
+def _doubles(buf, count):
+    """The first `count` doubles of a ctypes array made for this call."""
+    return np.frombuffer(buf, np.float64, count) if count else np.empty(0)
+
+
+_Slots = ctypes.c_double * CHEB_MAX_SLOTS
+_Rows = ctypes.c_double * (CHEB_MAX_OUTPUTS * CHEB_MAX_SLOTS)
 
 
 def cheb_version() -> int:
@@ -204,9 +239,8 @@ def cheb_chebyshev_nodes(n, kind=1, a=-1.0, b=1.0) -> np.ndarray:
 
 def cheb_combine(src_ptrs, w, out_ptr, numel, dtype, stream=0):
     w = _f64(w).reshape(-1)
-    arr = _voidp_array(src_ptrs)
-    _check(LIB.cheb_combine(arr, len(src_ptrs), _dptr(w), ctypes.c_void_p(int(out_ptr)),
-                            int(numel), int(dtype), ctypes.c_void_p(int(stream))))
+    _check(LIB.cheb_combine(_voidp_array(src_ptrs), len(src_ptrs), _dptr(w), int(out_ptr),
+                            int(numel), int(dtype), int(stream)))
 
 
 def cheb_combine_multi(src_ptrs, w, out_ptrs, numel, dtype, stream=0):
@@ -215,8 +249,7 @@ def cheb_combine_multi(src_ptrs, w, out_ptrs, numel, dtype, stream=0):
     n_out = len(out_ptrs)
     w = w.reshape(n_out, len(src_ptrs))
     _check(LIB.cheb_combine_multi(_voidp_array(src_ptrs), len(src_ptrs), _dptr(w), n_out,
-                                  _voidp_array(out_ptrs), int(numel), int(dtype),
-                                  ctypes.c_void_p(int(stream))))
+                                  _voidp_array(out_ptrs), int(numel), int(dtype), int(stream)))
 
 
 def cheb_cache_arena_bytes(n_slots, dtype, seg_numel):
@@ -287,8 +320,7 @@ def cheb_cache_reset(handle):
 
 
 def cheb_cache_push(handle, t, seg_ptrs, stream=0):
-    arr = _voidp_array(seg_ptrs)
-    _check(LIB.cheb_cache_push(handle, float(t), arr, ctypes.c_void_p(int(stream))))
+    _check(LIB.cheb_cache_push(handle, float(t), _voidp_array(seg_ptrs), int(stream)))
 
 
 def cheb_cache_begin_push(handle) -> int:
@@ -306,10 +338,10 @@ def cheb_cache_abort_push(h):
 
 
 def cheb_cache_history(handle, n_slots=CHEB_MAX_SLOTS):
-    t = np.empty(CHEB_MAX_SLOTS, dtype=np.float64)
+    t = _Slots()
     n = ctypes.c_int32()
-    _check(LIB.cheb_cache_history(handle, _dptr(t), ctypes.byref(n)))
-    return t[:n.value].copy()
+    _check(LIB.cheb_cache_history(handle, t, ctypes.byref(n)))
+    return _doubles(t, n.value)
 
 
 def cheb_cache_entry(handle, idx) -> int:
@@ -395,56 +427,49 @@ def cheb_table_load(path):
 
 def cheb_extrapolate_steps(handle, table, first_step, out_ptrs, stream=0):
     _check(LIB.cheb_extrapolate_steps(handle, table, int(first_step), len(out_ptrs),
-                                      _voidp_array(out_ptrs), ctypes.c_void_p(int(stream))))
+                                      _voidp_array(out_ptrs), int(stream)))
 
 
 def cheb_extrapolate(handle, w, out_ptr, stream=0):
     w = _f64(w).reshape(-1)
-    _check(LIB.cheb_extrapolate(handle, _dptr(w), ctypes.c_void_p(int(out_ptr)),
-                                ctypes.c_void_p(int(stream))))
+    _check(LIB.cheb_extrapolate(handle, _dptr(w), int(out_ptr), int(stream)))
 
 
 def cheb_extrapolate_at(handle, target_t, out_ptr, stream=0, n_slots=CHEB_MAX_SLOTS):
-    w = np.zeros(CHEB_MAX_SLOTS, dtype=np.float64)
-    _check(LIB.cheb_extrapolate_at(handle, float(target_t), ctypes.c_void_p(int(out_ptr)),
-                                   ctypes.c_void_p(int(stream)), _dptr(w)))
-    return w[:n_slots].copy()
+    w = _Slots()
+    _check(LIB.cheb_extrapolate_at(handle, float(target_t), int(out_ptr), int(stream), w))
+    return _doubles(w, n_slots)
 
 
 def cheb_extrapolate_multi(handle, w, out_ptrs, stream=0):
     """w: [n_out, n_slots] fp64, rows aligned with cheb_cache_history."""
     w = _f64(w).reshape(len(out_ptrs), -1)
     _check(LIB.cheb_extrapolate_multi(handle, _dptr(w), len(out_ptrs), _voidp_array(out_ptrs),
-                                      ctypes.c_void_p(int(stream))))
+                                      int(stream)))
 
 
 def cheb_extrapolate_at_multi(handle, targets, out_ptrs, stream=0, n_slots=CHEB_MAX_SLOTS):
     t = _f64(targets).reshape(-1)
     if t.size != len(out_ptrs):
         raise ChebError(CHEB_E_INVAL, "one output per target")
-    w = np.zeros((CHEB_MAX_OUTPUTS, CHEB_MAX_SLOTS), dtype=np.float64)
+    w = _Rows()
     _check(LIB.cheb_extrapolate_at_multi(handle, _dptr(t), t.size, _voidp_array(out_ptrs),
-                                         ctypes.c_void_p(int(stream)), _dptr(w)))
-    return w.reshape(-1)[:t.size * n_slots].reshape(t.size, n_slots).copy()
+                                         int(stream), w))
+    return _doubles(w, t.size * n_slots).reshape(t.size, n_slots)
 
 
 def cheb_residual_apply(handle, w, res_offset, res_numel, x_in_ptr, x_out_ptr, stream=0):
     w = _f64(w).reshape(-1)
-    ro = np.ascontiguousarray(res_offset, dtype=np.int64).reshape(-1)
-    _check(LIB.cheb_residual_apply(handle, _dptr(w), ro.ctypes.data_as(_i64p), int(res_numel),
-                                   ctypes.c_void_p(int(x_in_ptr or 0)),
-                                   ctypes.c_void_p(int(x_out_ptr)), ctypes.c_void_p(int(stream))))
+    _check(LIB.cheb_residual_apply(handle, _dptr(w), _i64ptr(res_offset)[0], int(res_numel),
+                                   int(x_in_ptr or 0), int(x_out_ptr), int(stream)))
 
 
 def cheb_residual_reduce(seg_ptrs, seg_numel, res_offset, dtype, x_in_ptr, x_out_ptr, res_numel,
                          stream=0):
-    sn = np.ascontiguousarray(seg_numel, dtype=np.int64).reshape(-1)
-    ro = np.ascontiguousarray(res_offset, dtype=np.int64).reshape(-1)
-    _check(LIB.cheb_residual_reduce(_voidp_array(seg_ptrs), sn.ctypes.data_as(_i64p),
-                                    ro.ctypes.data_as(_i64p), sn.size, int(dtype),
-                                    ctypes.c_void_p(int(x_in_ptr or 0)),
-                                    ctypes.c_void_p(int(x_out_ptr)), int(res_numel),
-                                    ctypes.c_void_p(int(stream))))
+    sn, n_segs = _i64ptr(seg_numel)
+    _check(LIB.cheb_residual_reduce(_voidp_array(seg_ptrs), sn, _i64ptr(res_offset)[0], n_segs,
+                                    int(dtype), int(x_in_ptr or 0), int(x_out_ptr),
+                                    int(res_numel), int(stream)))
 
 
 def cheb_get_launch_config():

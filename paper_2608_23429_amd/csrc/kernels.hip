@@ -866,7 +866,8 @@ int launch_combine(int dtype, const void *const *src, int n, const double *w, in
 // smaller one still costs its dispatch (about 4.7 blocks a nanosecond on
 // MI355X).  A launch is closed, largest segments first, before the blocks
 // without work would pass 16384, about what another launch costs (FLUX-1024:
-// two launches with 58K idle blocks of 1.6M in place of 525K of 2.1M).
+// three launches with 15K idle blocks of 1.6M in place of two with 525K of
+// 2.1M).
 int launch_gather(int dtype, void *slot_base, const GatherSeg *segs, int n_segs,
                   int64_t super_vecs, hipStream_t stream) {
   constexpr uint64_t kIdleBlocks = 16384;
