@@ -681,6 +681,14 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
   double acc[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] = 0.0;
+  u32x4 x1[W == 1 ? V / 4 : 1];  // one wave: the residual's own values, ahead of the history
+  if constexpr (W == 1) {
+#pragma unroll
+    for (int h = 0; h < V / 4; ++h) {
+      x1[h] = u32x4{0u, 0u, 0u, 0u};
+      if (a.x_in) x1[h] = *(reinterpret_cast<const u32x4 *>(a.x_in + (j0 + l) * V) + h);
+    }
+  }
   int32_t c = int32_t(wave) * U;
   for (; c + U <= nc; c += W * U) {
     u32x4 v[U][NS];
@@ -705,11 +713,10 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
     const uint64_t o = (j0 + lane) * V;
 #pragma unroll
     for (int h = 0; h < V; h += 4) {
-      u32x4 x = {0u, 0u, 0u, 0u}, r;
-      if (a.x_in) x = *reinterpret_cast<const u32x4 *>(a.x_in + o + h);
+      u32x4 r;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        r[q] = __float_as_uint(float(double(__uint_as_float(x[q])) + acc[h + q]));
+        r[q] = __float_as_uint(float(double(__uint_as_float(x1[h / 4][q])) + acc[h + q]));
       *reinterpret_cast<u32x4 *>(a.x_out + o + h) = r;
     }
   } else {
@@ -753,7 +760,11 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
 // 2 blocks, 1463 with 3, 1497 without a limit; one entry, 291 with 3, 294
 // with 4, 300 without; 15 segments, 15K tiles, 8 entries, 281 with 2 blocks,
 // 287 with 4; 3 segments, 52K tiles, 8 entries, 229 with 4 blocks of 2 waves,
-// 254 without a limit.
+// 254 without a limit.  A single segment (a collapsed history) is a stream of
+// ns reads plus the residual's own read and write per tile and takes about 80
+// KiB of those a compute unit (fp32, 225K tiles: 6 entries 395 us with 10
+// blocks, 413 without a limit; 8 entries 470 with 8, 495; bf16, 3 entries,
+// 112K tiles, 129 with 12, 133).
 struct ResShape {
   int waves;
   int blocks_per_cu;  // 0: no limit
@@ -761,6 +772,7 @@ struct ResShape {
 
 ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, int cus) {
   const uint32_t per_cu = tiles / uint32_t(cus);
+  if (ncover == 1 && per_cu >= 32) return {1, 80 / (ns + vec / 2)};
   if (ncover <= 1 || (ncover <= 4 && per_cu < 64)) return {1, 0};
   if (ncover == 2 && vec == 4) return {1, 0};
   if (ncover <= 4) return {2, ns >= 7 ? 4 : ns >= 3 ? 8 : 0};

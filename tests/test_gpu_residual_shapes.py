@@ -56,7 +56,7 @@ def test_small_residual(dtype, n, ncover):
 
 
 @pytest.mark.parametrize("layout", ["slots", "interleaved"])
-@pytest.mark.parametrize("n,ncover,vecs", [(1, 2, 64 * 64 * 256 + 1), (2, 3, 64 * 64 * 256 + 63),
+@pytest.mark.parametrize("n,ncover,vecs", [(4, 1, 32 * 64 * 256 + 1), (1, 2, 64 * 64 * 256 + 1), (2, 3, 64 * 64 * 256 + 63),
                                            (7, 5, 16 * 64 * 256 + 1), (6, 24, 16 * 64 * 256 + 2),
                                            (2, 9, 16 * 64 * 256 + 65), (3, 6, 64 * 300 + 31)])
 def test_many_tiles(layout, n, ncover, vecs):
