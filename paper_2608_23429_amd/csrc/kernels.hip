@@ -606,7 +606,7 @@ struct F32Dec {
 
 constexpr int kResCover = 128;
 constexpr int kResIntervals = kMaxResIntervals;
-constexpr int kResTile = 64;  // residual vectors per block, one per lane
+constexpr uint32_t kResTile = 64;  // residual vectors of a run, one per lane
 
 // One interval's part of a launch: tiles from `tile` on.
 struct ResPart {
@@ -627,33 +627,67 @@ struct ResArgs {
   uint64_t super;
 };
 
-// A tile's vectors of one covering segment: entry k's go to v[k].  The place
-// of the tile's first vector v0 is uniform (scalar arithmetic); a lane adds
-// its own index and, past the end of that vector's chunk, the jump to the entry's
-// next one (64 vectors span at most two chunks; for contiguous entries super
-// is kChunkVecs and there is no jump).
-template <int NS>
-__device__ __forceinline__ void res_load(u32x4 (&v)[NS], const ResArgs<NS> &a, uint64_t v0,
-                                         uint32_t lane) {
-  const uint32_t r = uint32_t(v0) & uint32_t(kChunkVecs - 1);
-  const uint64_t off = (v0 >> kChunkShift) * a.super + r;
-  const uint32_t l =
-      lane + (r + lane >= uint32_t(kChunkVecs) ? uint32_t(a.super - uint64_t(kChunkVecs)) : 0u);
+// A tile's vectors of one covering segment: entry k's of run i go to v[i][k].
+// The place of a run's first vector is uniform (scalar arithmetic); a lane
+// adds its own index and, past the end of that vector's chunk, the jump to
+// the entry's next one (64 vectors span at most two chunks; for contiguous
+// entries super is kChunkVecs and there is no jump).
+template <int NS, int T>
+__device__ __forceinline__ void res_load(u32x4 (&v)[T][NS], const ResArgs<NS> &a, uint64_t delta,
+                                         const uint64_t (&j0)[T], const uint32_t (&lane)[T]) {
+  uint64_t at[T];
+  uint32_t l[T];
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    // In the global address space: an address made from an integer is
-    // otherwise loaded as a flat one.
-    auto *p = reinterpret_cast<const __attribute__((address_space(1))) char *>(a.base[k] +
-                                                                              off * 16u);
-    v[k] = __builtin_nontemporal_load(
-        reinterpret_cast<const __attribute__((address_space(1))) u32x4 *>(p + l * 16u));
+  for (int i = 0; i < T; ++i) {
+    const uint64_t v0 = delta + j0[i];
+    const uint32_t r = uint32_t(v0) & uint32_t(kChunkVecs - 1);
+    at[i] = ((v0 >> kChunkShift) * a.super + r) * 16u;
+    l[i] = lane[i] +
+           (r + lane[i] >= uint32_t(kChunkVecs) ? uint32_t(a.super - uint64_t(kChunkVecs)) : 0u);
   }
+#pragma unroll
+  for (int k = 0; k < NS; ++k)
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      // In the global address space: an address made from an integer is
+      // otherwise loaded as a flat one.
+      auto *p = reinterpret_cast<const __attribute__((address_space(1))) char *>(a.base[k] + at[i]);
+      v[i][k] = __builtin_nontemporal_load(
+          reinterpret_cast<const __attribute__((address_space(1))) u32x4 *>(p + l[i] * 16u));
+    }
 }
 
-// Bound by HBM reads: NS x ncover loads of 1 KiB per tile of 64 residual
+// A tile is T runs of 64 vectors (T = 2: kResPair apart, or evenly apart in
+// what a part has left past its last whole pair of kResPair).
+constexpr uint32_t kResPair = 4096;
+
+struct ResTile {
+  uint32_t first;   // first vector of its first run, within the part
+  uint32_t stride;  // vectors from run to run
+};
+
+template <int T>
+__host__ __device__ inline uint32_t res_tiles(uint32_t n_vec) {
+  if (T == 1) return (n_vec + kResTile - 1) / kResTile;
+  const uint32_t rest = n_vec % (2 * kResPair);
+  return n_vec / (2 * kResPair) * (kResPair / kResTile) + ((rest + 1) / 2 + kResTile - 1) / kResTile;
+}
+
+template <int T>
+__device__ __forceinline__ ResTile res_tile(uint32_t tile, uint32_t n_vec) {
+  if (T == 1) return {tile * kResTile, 0};
+  constexpr uint32_t kPer = kResPair / kResTile;
+  const uint32_t whole = n_vec / (2 * kResPair);
+  if (tile < whole * kPer) return {tile / kPer * (2 * kResPair) + tile % kPer * kResTile, kResPair};
+  const uint32_t rest = n_vec % (2 * kResPair);
+  return {whole * (2 * kResPair) + (tile - whole * kPer) * kResTile,
+          ((rest + 1) / 2 + kResTile - 1) / kResTile * kResTile};
+}
+
+// Bound by HBM reads: NS x ncover loads of 1 KiB per run of 64 residual
 // vectors.  The W waves of a block take the covering segments in turn, U at
 // a time with all their loads ahead of the arithmetic, into fp64 partial
-// sums of the same 64 vectors, and add those up through LDS.  Dividing the
+// sums of the same vectors, and add those up through LDS.  Dividing the
 // segments among waves gives a small residual W times the waves to fill the
 // chip with, and has the blocks in flight read neighbouring kilobytes of a
 // few places at a time rather than 16 KiB runs of every place.  Measured on
@@ -661,7 +695,13 @@ __device__ __forceinline__ void res_load(u32x4 (&v)[NS], const ResArgs<NS> &a, u
 // FLUX-1024 cache, 6 interleaved entries, 1566 -> 1447 us (6.3 -> 6.8 TB/s);
 // DiT-XL/2 256 for one image (56 segments, 1152 tiles), 3 entries, 66 -> 35
 // us; an eighth of it (144 tiles), 54 -> 10 us.
-template <class Dec, int NS, int W, int U>
+// From contiguous memory a wave reads two runs 64 KiB apart (T = 2) at once:
+// kilobytes at that distance share open DRAM rows, which the many far places
+// a tile reads would otherwise close between them (FLUX-1024, 6 contiguous
+// entries, 1600 -> 1454 us; one entry, 292 -> 266; at 16 KiB apart 1.5 to 3%
+// less, at 128 KiB nothing).  Interleaved entries have that neighbourhood
+// already and lose 2% by it.
+template <class Dec, int NS, int W, int U, int T>
 __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
   constexpr int V = Dec::kVec;
   constexpr uint32_t kThreads = 64u * W;
@@ -671,114 +711,147 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
   for (int32_t q = 1; q < a.n_part; ++q)
     if (blockIdx.x >= a.part[q].tile) p = q;
   const ResPart part = a.part[p];
-  const uint32_t first = (blockIdx.x - part.tile) * uint32_t(kResTile);
-  const uint32_t left = part.n_vec - first;
-  const uint32_t live = left < uint32_t(kResTile) ? left : uint32_t(kResTile);  // vectors here
-  const uint32_t l = lane < live ? lane : live - 1u;  // idle lanes repeat the last vector
-  const uint64_t j0 = uint64_t(part.vec_begin) + first;
+  const ResTile tile = res_tile<T>(blockIdx.x - part.tile, part.n_vec);
+  uint32_t live[T], l[T];  // vectors of a run; a lane's own (idle lanes repeat the last)
+  uint64_t j0[T];
+#pragma unroll
+  for (int i = 0; i < T; ++i) {
+    const uint32_t first = tile.first + uint32_t(i) * tile.stride;
+    const uint32_t left = first < part.n_vec ? part.n_vec - first : 0u;
+    live[i] = left < kResTile ? left : kResTile;
+    // a run past the end reads the first one's place again
+    j0[i] = uint64_t(part.vec_begin) + (left ? first : tile.first);
+    const uint32_t run = left ? live[i] : live[0];
+    l[i] = lane < run ? lane : run - 1u;
+  }
   const int64_t *delta = a.delta + part.first;
   const int32_t nc = part.ncover;
-  double acc[V];
+  double acc[T][V];
 #pragma unroll
-  for (int e = 0; e < V; ++e) acc[e] = 0.0;
-  u32x4 x1[W == 1 ? V / 4 : 1];  // one wave: the residual's own values, ahead of the history
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[i][e] = 0.0;
+  u32x4 x1[W == 1 ? T * V / 4 : 1];  // one wave: the residual's own values, ahead of the history
   if constexpr (W == 1) {
 #pragma unroll
-    for (int h = 0; h < V / 4; ++h) {
+    for (int h = 0; h < T * V / 4; ++h) {
+      const int i = h / (V / 4);
       x1[h] = u32x4{0u, 0u, 0u, 0u};
-      if (a.x_in) x1[h] = *(reinterpret_cast<const u32x4 *>(a.x_in + (j0 + l) * V) + h);
+      if (a.x_in)
+        x1[h] = *(reinterpret_cast<const u32x4 *>(a.x_in + (j0[i] + l[i]) * V) + h % (V / 4));
     }
   }
   int32_t c = int32_t(wave) * U;
   for (; c + U <= nc; c += W * U) {
-    u32x4 v[U][NS];
+    u32x4 v[U][T][NS];
 #pragma unroll
-    for (int u = 0; u < U; ++u) res_load(v[u], a, uint64_t(delta[c + u]) + j0, l);
+    for (int u = 0; u < U; ++u) res_load(v[u], a, uint64_t(delta[c + u]), j0, l);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int k = 0; k < NS; ++k) Dec::add(acc, v[u][k], a.w[k]);
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int k = 0; k < NS; ++k) Dec::add(acc[i], v[u][i][k], a.w[k]);
   }
   if constexpr (U > 1) {
     for (; c < nc; ++c) {  // the last group, if it is this wave's and partial
-      u32x4 v[NS];
-      res_load(v, a, uint64_t(delta[c]) + j0, l);
+      u32x4 v[T][NS];
+      res_load(v, a, uint64_t(delta[c]), j0, l);
 #pragma unroll
-      for (int k = 0; k < NS; ++k) Dec::add(acc, v[k], a.w[k]);
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int k = 0; k < NS; ++k) Dec::add(acc[i], v[i][k], a.w[k]);
     }
   }
   if constexpr (W == 1) {
-    if (lane >= live) return;
-    const uint64_t o = (j0 + lane) * V;
 #pragma unroll
-    for (int h = 0; h < V; h += 4) {
+    for (int h = 0; h < T * V / 4; ++h) {
+      const int i = h / (V / 4), e = h % (V / 4) * 4;
+      if (lane >= live[i]) continue;
       u32x4 r;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        r[q] = __float_as_uint(float(double(__uint_as_float(x1[h / 4][q])) + acc[h + q]));
-      *reinterpret_cast<u32x4 *>(a.x_out + o + h) = r;
+        r[q] = __float_as_uint(float(double(__uint_as_float(x1[h][q])) + acc[i][e + q]));
+      *reinterpret_cast<u32x4 *>(a.x_out + (j0[i] + lane) * V + e) = r;
     }
   } else {
-    // Element e of the tile's vector i at [e * 64 + i]: consecutive lanes
-    // write consecutive words.
-    __shared__ double sums[W][kResTile * V];
+    // Element e of vector n of run i at [(i * V + e) * 64 + n]: consecutive
+    // lanes write consecutive words.
+    __shared__ double sums[W][T * V * kResTile];
 #pragma unroll
-    for (int e = 0; e < V; ++e) sums[wave][e * kResTile + lane] = acc[e];
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int e = 0; e < V; ++e) sums[wave][(i * V + e) * int(kResTile) + lane] = acc[i][e];
     __syncthreads();
-    for (uint32_t h = threadIdx.x; h < live * uint32_t(V / 4); h += kThreads) {
-      const uint64_t o = j0 * V + 4u * h;
-      const uint32_t at = (4u * h % V) * kResTile + 4u * h / V;
-      u32x4 x = {0u, 0u, 0u, 0u}, r;
-      if (a.x_in) x = *reinterpret_cast<const u32x4 *>(a.x_in + o);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double s = double(__uint_as_float(x[q]));
+    for (int i = 0; i < T; ++i)
+      for (uint32_t h = threadIdx.x; h < live[i] * uint32_t(V / 4); h += kThreads) {
+        const uint64_t o = j0[i] * V + 4u * h;
+        const uint32_t at = (uint32_t(i * V) + 4u * h % V) * kResTile + 4u * h / V;
+        u32x4 x = {0u, 0u, 0u, 0u}, r;
+        if (a.x_in) x = *reinterpret_cast<const u32x4 *>(a.x_in + o);
 #pragma unroll
-        for (int w = 0; w < W; ++w) s += sums[w][at + q * kResTile];
-        r[q] = __float_as_uint(float(s));
+        for (int q = 0; q < 4; ++q) {
+          double s = double(__uint_as_float(x[q]));
+#pragma unroll
+          for (int w = 0; w < W; ++w) s += sums[w][at + uint32_t(q) * kResTile];
+          r[q] = __float_as_uint(float(s));
+        }
+        *reinterpret_cast<u32x4 *>(a.x_out + o) = r;
       }
-      *reinterpret_cast<u32x4 *>(a.x_out + o) = r;
-    }
   }
 }
 
-// Waves per block and how many of its blocks share a compute unit, from the
-// sizes (measured on MI355X, 256 compute units, bf16, interleaved entries):
-//  - fewer tiles than compute units: 16 waves (144 tiles of 56 segments, 3
-//    entries: 10 us against 16 with 4);
-//  - up to 4 segments: little to divide.  One wave, which needs no LDS sum
-//    (4 segments, 4.6K tiles, 3 entries: 14 us against 16 with 4 waves); two
+// Waves per block, how many of its blocks share a compute unit and runs per
+// tile, from the sizes (measured on MI355X, 256 compute units, bf16 unless
+// said; cu = tiles of one run per compute unit):
+//  - one segment (a collapsed history) is a stream of ns reads plus the
+//    residual's own read and write: one wave, about 80 KiB of those a compute
+//    unit (fp32, 225K tiles: 6 entries 395 us with 10 blocks, 413 without a
+//    limit; 8 entries 470 with 8, 495);
+//  - up to 4 segments: little to divide.  One wave, which needs no LDS sum (4
+//    segments, 4.6K tiles, 3 entries: 14 us against 16 with 4 waves); two
 //    where the residual is large (3 segments, 52K tiles, 2 entries: 89 us
-//    against 91; 2 segments, 37K tiles, one entry: 27.8 against 29.6, but
-//    42 against 38 in fp32, whose tiles are half as large);
-//  - otherwise 4 waves, and 8 for 7 entries or more (15 segments, 15K tiles,
-//    contiguous: 307 us against 311).
-// Where there are tiles for many rounds the blocks in flight are limited,
-// more for more entries and segments, so that the reads of a moment stay
-// close together: FLUX-1024 (57 segments, 27K tiles), 6 entries, 1446 us with
-// 2 blocks, 1463 with 3, 1497 without a limit; one entry, 291 with 3, 294
-// with 4, 300 without; 15 segments, 15K tiles, 8 entries, 281 with 2 blocks,
-// 287 with 4; 3 segments, 52K tiles, 8 entries, 229 with 4 blocks of 2 waves,
-// 254 without a limit.  A single segment (a collapsed history) is a stream of
-// ns reads plus the residual's own read and write per tile and takes about 80
-// KiB of those a compute unit (fp32, 225K tiles: 6 entries 395 us with 10
-// blocks, 413 without a limit; 8 entries 470 with 8, 495; bf16, 3 entries,
-// 112K tiles, 129 with 12, 133).
+//    against 91; but 2 segments in fp32, whose tiles are half as large, 42
+//    against 38);
+//  - below that: 16 waves under one tile a compute unit (144 tiles of 56
+//    segments, 3 entries: 10 us against 16 with 4), 4 under 4, 2 under 8 (1152
+//    tiles, 3 entries: 31.9 us against 33.2 with 4);
+//  - then contiguous entries take pairs of runs: one wave without a limit
+//    under cu = 32, the first third of it with single runs (2304 tiles, 3
+//    entries: 61 us against 65 with 4 waves; 6072 tiles of 24 segments, 6
+//    entries: 140 against 147), and 4 waves with few blocks beyond (9072
+//    tiles of 57 segments, 3 entries: 251 us with 2 blocks, 262 with 4 of
+//    single runs; 15 segments, 2 entries: 84 with 4, 99 with 2), but 2 waves
+//    for one entry and few segments (8 segments, 18K tiles: 35 us against 43);
+//  - interleaved entries 4 waves (8 for 7 entries or more), their blocks
+//    limited where there are many tiles (FLUX-1024, 57 segments, 27K tiles, 6
+//    entries: 1446 us with 2 blocks, 1463 with 3, 1497 without a limit; 15
+//    segments, 15K tiles, 8 entries: 281 with 2, 287 with 4).
 struct ResShape {
   int waves;
   int blocks_per_cu;  // 0: no limit
+  int runs = 1;
 };
 
-ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, int cus) {
+ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, bool contiguous, int cus) {
   const uint32_t per_cu = tiles / uint32_t(cus);
   if (ncover == 1 && per_cu >= 32) return {1, 80 / (ns + vec / 2)};
   if (ncover <= 1 || (ncover <= 4 && per_cu < 64)) return {1, 0};
   if (ncover == 2 && vec == 4) return {1, 0};
+  if (ncover <= 4 && contiguous) return {2, ns >= 5 ? 4 : 0, 2};
   if (ncover <= 4) return {2, ns >= 7 ? 4 : ns >= 3 ? 8 : 0};
   if (per_cu < 1 && ncover >= 16) return {16, 0};
+  if (per_cu < 4) return {4, 0};
+  if (per_cu < 8) return {2, 0};
+  if (contiguous) {
+    if (per_cu < 32) return {1, 0, per_cu < 12 ? 1 : 2};
+    if (ns == 1) return ncover >= 24 ? ResShape{4, 3, 2} : ResShape{2, 0, 2};
+    if (ns >= 5) return {4, 2, 2};
+    return {4, ncover < 32 ? 4 : ns == 2 ? 3 : 2, 2};
+  }
   if (per_cu < 16) return {4, 0};
-  if (ns == 1) return {4, ncover >= 24 ? 3 : 0};
   if (ns >= 7) return {8, 2};
   return {4, ncover >= 24 ? std::max(2, 4 - ns / 2) : 4};
 }
@@ -798,8 +871,6 @@ struct ResJob {
 
 template <class Dec, int NS>
 hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
-  // Segments a wave loads before its arithmetic.
-  constexpr int U = NS == 1 ? 4 : NS == 2 ? 2 : 1;
   ResArgs<NS> a;
   memset(&a, 0, sizeof a);
   a.super = j.super;
@@ -809,28 +880,44 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
   a.x_in = j.x_in;
   a.x_out = j.x_out;
   a.n_part = j.n_iv;
-  uint32_t tiles = 0;
+  uint32_t singles = 0;
   int ncover = 0;
+  for (int i = 0; i < j.n_iv; ++i) {
+    singles += res_tiles<1>(uint32_t(j.iv[i].n_vec));
+    ncover = std::max(ncover, int(j.iv[i].ncover));
+  }
+  const ResShape shape =
+      residual_shape(NS, Dec::kVec, ncover, singles, j.super == uint64_t(kChunkVecs), g.cus);
+  uint32_t tiles = 0;
   for (int i = 0, first = 0; i < j.n_iv; first += j.iv[i].ncover, ++i) {
     const uint32_t n_vec = uint32_t(j.iv[i].n_vec);
     a.part[i] = ResPart{tiles, uint32_t(j.iv[i].vec_begin), n_vec, first, j.iv[i].ncover};
-    tiles += (n_vec + uint32_t(kResTile) - 1) / uint32_t(kResTile);
-    ncover = std::max(ncover, int(j.iv[i].ncover));
+    tiles += shape.runs == 2 ? res_tiles<2>(n_vec) : res_tiles<1>(n_vec);
   }
-  const ResShape shape = residual_shape(NS, Dec::kVec, ncover, tiles, g.cus);
-  auto launch = [&](auto waves) {
-    constexpr int W = decltype(waves)::value;
-    constexpr size_t kOwn = W > 1 ? size_t(W) * kResTile * Dec::kVec * sizeof(double) : 0;
+  auto launch = [&](auto waves, auto runs) {
+    constexpr int W = decltype(waves)::value, T = decltype(runs)::value;
+    // Segments a wave loads before its arithmetic.
+    constexpr int U = NS == 1 ? 4 / T : NS == 2 ? (T == 2 && W == 1 ? 1 : 2) : 1;
+    constexpr size_t kOwn = W > 1 ? size_t(W) * T * kResTile * Dec::kVec * sizeof(double) : 0;
     const size_t share = lds_share(g.lds_per_cu, shape.blocks_per_cu);
     const size_t extra = share > kOwn ? share - kOwn : 0;
-    hipLaunchKernelGGL((residual_kernel<Dec, NS, W, U>), dim3(tiles), dim3(64 * W), extra, s, a);
+    hipLaunchKernelGGL((residual_kernel<Dec, NS, W, U, T>), dim3(tiles), dim3(64 * W), extra, s, a);
   };
-  if (shape.waves == 1) launch(std::integral_constant<int, 1>());
-  if (shape.waves == 2) launch(std::integral_constant<int, 2>());
-  if (shape.waves == 4) launch(std::integral_constant<int, 4>());
-  if constexpr (NS >= 7)
-    if (shape.waves == 8) launch(std::integral_constant<int, 8>());
-  if (shape.waves == 16) launch(std::integral_constant<int, 16>());
+  const std::integral_constant<int, 1> one;
+  const std::integral_constant<int, 2> two;
+  const std::integral_constant<int, 4> four;
+  switch (shape.runs * 100 + shape.waves) {
+    case 101: launch(one, one); break;
+    case 102: launch(two, one); break;
+    case 104: launch(four, one); break;
+    case 201: launch(one, two); break;
+    case 202: launch(two, two); break;
+    case 204: launch(four, two); break;
+    case 116: launch(std::integral_constant<int, 16>(), one); break;
+    default:  // 8 waves
+      if constexpr (NS >= 7) launch(std::integral_constant<int, 8>(), one);
+      break;
+  }
   return hipGetLastError();
 }
 

@@ -58,11 +58,26 @@ def test_small_residual(dtype, n, ncover):
 @pytest.mark.parametrize("layout", ["slots", "interleaved"])
 @pytest.mark.parametrize("n,ncover,vecs", [(4, 1, 32 * 64 * 256 + 1), (1, 2, 64 * 64 * 256 + 1), (2, 3, 64 * 64 * 256 + 63),
                                            (7, 5, 16 * 64 * 256 + 1), (6, 24, 16 * 64 * 256 + 2),
-                                           (2, 9, 16 * 64 * 256 + 65), (3, 6, 64 * 300 + 31)])
+                                           (2, 9, 16 * 64 * 256 + 65), (3, 6, 64 * 300 + 31),
+                                           (3, 5, 4 * 64 * 256 + 7), (3, 5, 8 * 64 * 256 + 7),
+                                           (2, 33, 32 * 64 * 256 + 9), (1, 24, 32 * 64 * 256 + 1),
+                                           (1, 5, 32 * 64 * 256 + 1)])
 def test_many_tiles(layout, n, ncover, vecs):
     """Residuals past each size at which the rule changes; odd vector counts
     put later segments' tiles across chunk ends."""
     _check("bf16", n, [vecs * 8] * ncover, [0] * ncover, vecs * 8, layout, True, ncover)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [1, 2, 5])
+@pytest.mark.parametrize("extra", [0, 1, 63, 64, 65, 128, 4095, 4096, 4097, 8191])
+def test_pairs_of_runs(dtype, n, extra):
+    """Contiguous entries in pairs of runs 4096 vectors apart: whole pairs of
+    4096 and every kind of rest behind them (none, one run, odd, one vector
+    short of whole)."""
+    vec = 4 if dtype == "f32" else 8
+    vecs = 26 * 8192 + extra                   # over 12 tiles a compute unit
+    _check(dtype, n, [vecs * vec] * 5, [0] * 5, vecs * vec, "slots", extra % 2 == 0, extra)
 
 
 @pytest.mark.parametrize("layout", ["slots", "interleaved"])
