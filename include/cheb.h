@@ -533,12 +533,13 @@ CHEB_API int cheb_residual_reduce(const void *const *seg_src, const int64_t *seg
  *   waves_per_cu  cap on the prediction kernel's 64-lane waves resident on
  *                one compute unit.  0: chosen, for the default shape from
  *                the history size n, the number of outputs m, the layout and
- *                the work (6 entries, one output: 8, or 7 interleaved; 5: 9
- *                and 8; several outputs: 60/(n+m) rounded, at least 6 to 8;
- *                no cap for n <= 2 and one output; twice as many for a call
- *                of under 512 KiB a compute unit), for the others max(6,
- *                44/n rounded) for one output and max(6, 36/n rounded) for
- *                several, no cap for n <= 2; -1: no cap; 1..32: that cap.
+ *                the work (6 entries, one output: 8, or 7 interleaved; no
+ *                cap for n <= 2 and one output; twice as many for a call of
+ *                under 512 KiB a compute unit; about half where a wave takes
+ *                two vectors per lane, in large calls over contiguous entries
+ *                with several outputs or 3 to 5 entries), for the others
+ *                max(6, 44/n rounded) for one output and max(6, 36/n rounded)
+ *                for several, no cap for n <= 2; -1: no cap; 1..32: that cap.
  *                Each block reserves an equal share of the compute unit's
  *                LDS, rounded down to the hardware's unit of it, which the
  *                kernel never touches, so that no more blocks fit; the cap

@@ -70,6 +70,36 @@ __device__ __forceinline__ uint64_t lane_vec(uint64_t v, uint64_t super) {
   return (v >> kChunkShift) * super + (v & uint64_t(kChunkVecs - 1));
 }
 
+// Tiles of R (one or two) runs of 64 vectors: a tile's runs lie 2^lg vectors
+// from one another, R 2^lg vectors after R 2^lg vectors; what is left
+// past the last whole R 2^lg is divided evenly.
+constexpr uint32_t kRun = 64;
+constexpr uint32_t kRunLg = 6;
+
+struct RunTile {
+  uint32_t first;   // first vector of its first run
+  uint32_t stride;  // vectors from run to run
+};
+
+template <int R>
+__host__ __device__ inline uint32_t run_tiles(uint32_t n_vec, uint32_t lg) {
+  if (R == 1) return (n_vec + kRun - 1) / kRun;
+  const uint32_t span = uint32_t(R) << lg, rest = n_vec & (span - 1);
+  return n_vec / span * ((1u << lg) / kRun) + ((rest + R - 1) / R + kRun - 1) / kRun;
+}
+
+template <int R>
+__device__ __forceinline__ RunTile run_tile(uint32_t tile, uint32_t n_vec, uint32_t lg) {
+  if constexpr (R == 1) return {tile * kRun, 0};
+  static_assert(R <= 2, "one or two runs");
+  constexpr uint32_t kLgR = 1;
+  const uint32_t whole = n_vec >> (lg + kLgR), span = tile >> (lg - kRunLg);
+  const uint32_t base = span << (lg + kLgR);
+  // The rest is shorter than a span, and so are its tiles: span == whole.
+  const uint32_t even = ((n_vec - base + R - 1) / R + kRun - 1) / kRun * kRun;
+  return {base + (tile & ((1u << (lg - kRunLg)) - 1u)) * kRun, span < whole ? 1u << lg : even};
+}
+
 // Ragged end of a stateless combination: `count` (< elements per vector)
 // trailing elements starting at element `first`, done by block 0.
 struct Tail {
@@ -205,42 +235,42 @@ struct F32Op {
 
 // ---- the streaming kernels -------------------------------------------------
 //
-// The default: one-wave blocks, each a tile of 64 vectors, so every load or
-// store instruction covers 1 KiB contiguous.  The tile's place in the history
-// is uniform (a chunk holds 32 tiles, none crosses one), so it is scalar
-// arithmetic and a load takes a scalar base and the lane's offset.  A
-// scheduling barrier keeps all NS loads ahead of the arithmetic.  With NO > 1
-// the loaded history feeds NO weight rows and NO outputs: every skipped step
-// between two full steps is predicted in one pass.  Bound by HBM: NS KiB read
-// and NO KiB written per block and next to no arithmetic; how many blocks
-// share a compute unit (auto_waves) decides how well reads and writes mix.
-// The last block takes the vectors past the last whole tile and the ragged
-// tail, which only contiguous sources have.
-template <class Op, int NS, int NO, bool NT>
+// The default: one-wave blocks, each a tile of R runs of 64 vectors, so every
+// load or store instruction covers 1 KiB contiguous.  A run's place in the
+// history is uniform (a chunk holds 32 runs, none crosses one), so it is
+// scalar arithmetic and a load takes a scalar base and the lane's offset.  A
+// scheduling barrier keeps all NS x R loads ahead of the arithmetic.  With NO
+// > 1 the loaded history feeds NO weight rows and NO outputs: every skipped
+// step between two full steps is predicted in one pass.  Bound by HBM: NS KiB
+// read and NO KiB written per run and next to no arithmetic; how many blocks
+// share a compute unit and how far a tile's runs lie apart (stream_shape)
+// decide how well reads and writes mix.  The ragged tail, which only
+// contiguous sources have, is a block of its own past the tiles; that block's
+// runs end past n_vec too, so whole tiles go without a test for it.
+template <class Op, int NS, int NO, int R, bool NT>
 __global__ __launch_bounds__(64) void stream_kernel(Hist<NS, NO, typename Op::W> h, uint32_t n_vec,
-                                                    Tail tail) {
-  const uint32_t first = blockIdx.x * 64u;
+                                                    uint32_t n_tiles, uint32_t lg, Tail tail) {
   const uint32_t lane = threadIdx.x;
-  const uint64_t at = lane_vec(first, h.super);
-  if (first + 64u <= n_vec) {
-    u32x4 v[NS];
+  const RunTile tile = run_tile<R>(blockIdx.x, n_vec, lg);
+  if (tile.first + uint32_t(R - 1) * tile.stride + kRun <= n_vec) {
+    u32x4 v[R][NS];
 #pragma unroll
-    for (int k = 0; k < NS; ++k) v[k] = load16<NT>(h.p[k] + at + lane);
+    for (int k = 0; k < NS; ++k)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        v[r][k] = load16<NT>(h.p[k] + lane_vec(tile.first + uint32_t(r) * tile.stride, h.super) +
+                             lane);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < NO; ++m)
-      store16<NT>(h.o[m] + first + lane, Op::template vec<NS>(v, h.w[m]));
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        store16<NT>(h.o[m] + tile.first + uint32_t(r) * tile.stride + lane,
+                    Op::template vec<NS>(v[r], h.w[m]));
     return;
   }
-  if (first + lane < n_vec) {
-    u32x4 v[NS];
-#pragma unroll
-    for (int k = 0; k < NS; ++k) v[k] = load16<NT>(h.p[k] + at + lane);
-#pragma unroll
-    for (int m = 0; m < NO; ++m)
-      store16<NT>(h.o[m] + first + lane, Op::template vec<NS>(v, h.w[m]));
-  }
-  if (lane < tail.count) {
+  if (blockIdx.x == n_tiles) {
+    if (lane >= tail.count) return;
     using E = typename Op::E;
     const E *p[NS];
 #pragma unroll
@@ -249,6 +279,18 @@ __global__ __launch_bounds__(64) void stream_kernel(Hist<NS, NO, typename Op::W>
 #pragma unroll
     for (int m = 0; m < NO; ++m)
       reinterpret_cast<E *>(h.o[m])[i] = Op::template scalar<NS>(p, h.w[m], i);
+    return;
+  }
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    const uint32_t first = tile.first + uint32_t(r) * tile.stride;
+    if (first + lane >= n_vec) return;
+    u32x4 v[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) v[k] = load16<NT>(h.p[k] + lane_vec(first, h.super) + lane);
+#pragma unroll
+    for (int m = 0; m < NO; ++m)
+      store16<NT>(h.o[m] + first + lane, Op::template vec<NS>(v, h.w[m]));
   }
 }
 
@@ -322,22 +364,40 @@ struct Gpu {
   int waves;       // occupancy cap in waves per compute unit, 0: none
 };
 
-// One-wave blocks that share a compute unit, from the history size, the
-// number of outputs, the layout and the work (0: no limit).  Too few leave the
-// memory latency uncovered, too many flood the memory queues and slow the
-// writes.  Measured on MI355X, bf16, entries of 0.1 to 1.6 GB, within 3% of
-// the best of 5 to 25 blocks and none:
+// Runs per tile, the distance between them and how many one-wave blocks share
+// a compute unit (0: no limit), from the history size, the number of outputs,
+// the layout and the work.  Too few blocks leave the memory latency uncovered,
+// too many flood the memory queues and slow the writes.  Measured on MI355X,
+// bf16, entries of 0.1 to 1.6 GB, single runs within 3% of the best of 5 to
+// 25 blocks and none:
 //  - one output: about 40 KiB of loads in flight from interleaved entries, 45
 //    to 48 from contiguous ones (6 interleaved entries of 1.6 GB: 1627 us with
 //    7, 1642 with 6, over 1670 with 8; 5 contiguous ones: 1417 us with 9, 1447
-//    with 10); up to two entries stream as well without a limit;
+//    with 10);
 //  - several outputs: about 60 KiB of loads and stores (2 entries, 5 outputs
 //    of 264 MB: 291 us with 9, 299 with 12, 319 without a limit), and not
 //    below 6 to 8;
 //  - a call of under 512 KiB a compute unit is over before the queues fill
 //    and wants twice as many (6 entries of 9 MB: 11.4 us with 16, 12.6 with
-//    7).
-int stream_blocks(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
+//    7);
+//  - above that, contiguous entries in tiles of two runs 64 KiB apart, which
+//    share DRAM rows, for several outputs and for one output of 3 to 5
+//    entries (2 entries, 5 outputs of 264 MB: 289 us -> 282; 6 entries, 3
+//    outputs of 1.06 GB in fp16: 1452 -> 1434; 3 entries of 264 MB 159 -> 154;
+//    5 of 528 MB 473 -> 467).  One output of 6 entries or more loses 2% by it,
+//    interleaved entries gain nothing, and one or two entries 1%.
+struct StreamShape {
+  int blocks_per_cu;  // 0: no limit
+  int runs = 1;
+  uint32_t lg = kRunLg;  // of the vectors from run to run
+};
+
+bool large_call(int ns, int no, uint32_t n_vec, int cus) {
+  return uint64_t(n_vec / kRun) * uint64_t(ns + no) >= 512u * uint64_t(cus);
+}
+
+// Blocks of single runs.
+int single_blocks(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
   static constexpr int kOne[2][CHEB_MAX_SLOTS + 1] = {{0, 0, 0, 16, 11, 9, 8, 7, 6},
                                                       {0, 0, 0, 14, 9, 8, 7, 6, 5}};
   const int sum = ns + no;
@@ -346,8 +406,17 @@ int stream_blocks(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
     const int least = sum >= 12 ? 6 : sum <= 9 && !interleaved ? 8 : 7;
     blocks = std::max(least, (60 + sum / 2) / sum);
   }
-  const uint64_t kib_per_cu = uint64_t(n_vec / 64u) * uint64_t(sum) / uint64_t(cus);
-  return kib_per_cu < 512 ? 2 * blocks : blocks;
+  return large_call(ns, no, n_vec, cus) ? blocks : 2 * blocks;
+}
+
+StreamShape stream_shape(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
+  if (large_call(ns, no, n_vec, cus)) {
+    const int sum = ns + no;
+    if (!interleaved && no > 1)
+      return {std::max(sum >= 14 ? 4 : 5, (36 + sum / 2) / sum), 2, 12};
+    if (!interleaved && ns >= 3 && ns <= 5) return {(28 + sum / 2) / sum, 2, 12};
+  }
+  return {single_blocks(ns, no, interleaved, n_vec, cus)};
 }
 
 // Waves per compute unit of the other launch shapes, whose loops and larger
@@ -399,16 +468,30 @@ hipError_t launch_shape(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, T
   return hipGetLastError();
 }
 
-// The default launch shape: one-wave blocks, as many of them on a compute
-// unit as dev.waves says.
+// The default launch shape.
+template <class Op, int NS, int NO, int R, bool NT>
+hipError_t launch_runs(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, Tail tail,
+                       int blocks, uint32_t lg, const Gpu &g, hipStream_t s) {
+  const uint32_t tiles = run_tiles<R>(n_vec, lg);
+  hipLaunchKernelGGL((stream_kernel<Op, NS, NO, R, NT>), dim3(tiles + (tail.count != 0 ? 1u : 0u)),
+                     dim3(64), blocks > 2 && blocks < 32 ? lds_share(g.lds_per_cu, blocks) : 0, s,
+                     h, n_vec, tiles, lg, tail);
+  return hipGetLastError();
+}
+
 template <class Op, int NS, int NO, bool NT>
 hipError_t launch_stream(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, Tail tail,
-                         const Gpu &g, hipStream_t s) {
-  const uint32_t grid = n_vec / 64u + (n_vec % 64u != 0 || tail.count != 0 ? 1u : 0u);
-  hipLaunchKernelGGL((stream_kernel<Op, NS, NO, NT>), dim3(grid), dim3(64),
-                     g.waves > 2 && g.waves < 32 ? lds_share(g.lds_per_cu, g.waves) : 0, s, h, n_vec,
-                     tail);
-  return hipGetLastError();
+                         const cheb_launch_config &cfg, const Gpu &g, hipStream_t s) {
+  if constexpr (NT) {
+    if (cfg.waves_per_cu == 0) {
+      const StreamShape shape =
+          stream_shape(NS, NO, h.super != uint64_t(kChunkVecs), n_vec, g.cus);
+      if (shape.runs == 2)
+        return launch_runs<Op, NS, NO, 2, NT>(h, n_vec, tail, shape.blocks_per_cu, shape.lg, g, s);
+      return launch_runs<Op, NS, NO, 1, NT>(h, n_vec, tail, shape.blocks_per_cu, kRunLg, g, s);
+    }
+  }
+  return launch_runs<Op, NS, NO, 1, NT>(h, n_vec, tail, g.waves, kRunLg, g, s);
 }
 
 // Single output: every launch shape of the tuning interface.
@@ -419,7 +502,7 @@ hipError_t launch_one(const Hist<NS, 1, typename Op::W> &h, uint32_t n_vec, Tail
   // A problem too small to give every compute unit a few 1024-thread blocks
   // runs with 256-thread blocks instead (four times as many blocks).
   const bool small = uint64_t(n_vec) < uint64_t(4 * 1024) * uint64_t(dev.cus);
-  if (b == 64 && g == 0) return launch_stream<Op, NS, 1, NT>(h, n_vec, tail, dev, s);
+  if (b == 64 && g == 0) return launch_stream<Op, NS, 1, NT>(h, n_vec, tail, cfg, dev, s);
   if (b == 64) return launch_shape<Op, NS, 1, 64, 1, NT>(h, n_vec, tail, g, dev, s);
   if (b == 1024 && small) return launch_shape<Op, NS, 1, 256, 1, NT>(h, n_vec, tail, g, dev, s);
   if (b == 1024) return launch_shape<Op, NS, 1, 1024, 1, NT>(h, n_vec, tail, g, dev, s);
@@ -439,8 +522,8 @@ template <class Op, int NS, int NO>
 hipError_t launch_many(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, Tail tail,
                        const cheb_launch_config &cfg, const Gpu &dev, hipStream_t s) {
   if (cfg.block == 64)
-    return cfg.nontemporal ? launch_stream<Op, NS, NO, true>(h, n_vec, tail, dev, s)
-                           : launch_stream<Op, NS, NO, false>(h, n_vec, tail, dev, s);
+    return cfg.nontemporal ? launch_stream<Op, NS, NO, true>(h, n_vec, tail, cfg, dev, s)
+                           : launch_stream<Op, NS, NO, false>(h, n_vec, tail, cfg, dev, s);
   return cfg.nontemporal ? launch_shape<Op, NS, NO, 1024, 1, true>(h, n_vec, tail, 0, dev, s)
                          : launch_shape<Op, NS, NO, 1024, 1, false>(h, n_vec, tail, 0, dev, s);
 }
@@ -462,7 +545,7 @@ hipError_t launch_ns_no(const void *const *src, const double *w, void *const *ou
   if (cfg.waves_per_cu != 0)
     dev.waves = std::max(0, cfg.waves_per_cu);
   else if (cfg.block == 64 && cfg.blocks_per_cu == 0)
-    dev.waves = stream_blocks(NS, NO, super_vecs != kChunkVecs, n_vec, dev.cus);
+    dev.waves = single_blocks(NS, NO, super_vecs != kChunkVecs, n_vec, dev.cus);
   else
     dev.waves = auto_waves(NS, NO);
   Tail tail{uint32_t(numel % kVec), uint64_t(numel / kVec) * kVec};
@@ -606,7 +689,6 @@ struct F32Dec {
 
 constexpr int kResCover = 128;
 constexpr int kResIntervals = kMaxResIntervals;
-constexpr uint32_t kResTile = 64;  // residual vectors of a run, one per lane
 
 // One interval's part of a launch: tiles from `tile` on.
 struct ResPart {
@@ -657,32 +739,7 @@ __device__ __forceinline__ void res_load(u32x4 (&v)[T][NS], const ResArgs<NS> &a
     }
 }
 
-// A tile is T runs of 64 vectors (T = 2: kResPair apart, or evenly apart in
-// what a part has left past its last whole pair of kResPair).
-constexpr uint32_t kResPair = 4096;
-
-struct ResTile {
-  uint32_t first;   // first vector of its first run, within the part
-  uint32_t stride;  // vectors from run to run
-};
-
-template <int T>
-__host__ __device__ inline uint32_t res_tiles(uint32_t n_vec) {
-  if (T == 1) return (n_vec + kResTile - 1) / kResTile;
-  const uint32_t rest = n_vec % (2 * kResPair);
-  return n_vec / (2 * kResPair) * (kResPair / kResTile) + ((rest + 1) / 2 + kResTile - 1) / kResTile;
-}
-
-template <int T>
-__device__ __forceinline__ ResTile res_tile(uint32_t tile, uint32_t n_vec) {
-  if (T == 1) return {tile * kResTile, 0};
-  constexpr uint32_t kPer = kResPair / kResTile;
-  const uint32_t whole = n_vec / (2 * kResPair);
-  if (tile < whole * kPer) return {tile / kPer * (2 * kResPair) + tile % kPer * kResTile, kResPair};
-  const uint32_t rest = n_vec % (2 * kResPair);
-  return {whole * (2 * kResPair) + (tile - whole * kPer) * kResTile,
-          ((rest + 1) / 2 + kResTile - 1) / kResTile * kResTile};
-}
+constexpr uint32_t kResPairLg = 12;  // pairs of runs lie 4096 vectors (64 KiB) apart
 
 // Bound by HBM reads: NS x ncover loads of 1 KiB per run of 64 residual
 // vectors.  The W waves of a block take the covering segments in turn, U at
@@ -711,14 +768,14 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
   for (int32_t q = 1; q < a.n_part; ++q)
     if (blockIdx.x >= a.part[q].tile) p = q;
   const ResPart part = a.part[p];
-  const ResTile tile = res_tile<T>(blockIdx.x - part.tile, part.n_vec);
+  const RunTile tile = run_tile<T>(blockIdx.x - part.tile, part.n_vec, kResPairLg);
   uint32_t live[T], l[T];  // vectors of a run; a lane's own (idle lanes repeat the last)
   uint64_t j0[T];
 #pragma unroll
   for (int i = 0; i < T; ++i) {
     const uint32_t first = tile.first + uint32_t(i) * tile.stride;
     const uint32_t left = first < part.n_vec ? part.n_vec - first : 0u;
-    live[i] = left < kResTile ? left : kResTile;
+    live[i] = left < kRun ? left : kRun;
     // a run past the end reads the first one's place again
     j0[i] = uint64_t(part.vec_begin) + (left ? first : tile.first);
     const uint32_t run = left ? live[i] : live[0];
@@ -778,24 +835,24 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
   } else {
     // Element e of vector n of run i at [(i * V + e) * 64 + n]: consecutive
     // lanes write consecutive words.
-    __shared__ double sums[W][T * V * kResTile];
+    __shared__ double sums[W][T * V * kRun];
 #pragma unroll
     for (int i = 0; i < T; ++i)
 #pragma unroll
-      for (int e = 0; e < V; ++e) sums[wave][(i * V + e) * int(kResTile) + lane] = acc[i][e];
+      for (int e = 0; e < V; ++e) sums[wave][(i * V + e) * int(kRun) + lane] = acc[i][e];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < T; ++i)
       for (uint32_t h = threadIdx.x; h < live[i] * uint32_t(V / 4); h += kThreads) {
         const uint64_t o = j0[i] * V + 4u * h;
-        const uint32_t at = (uint32_t(i * V) + 4u * h % V) * kResTile + 4u * h / V;
+        const uint32_t at = (uint32_t(i * V) + 4u * h % V) * kRun + 4u * h / V;
         u32x4 x = {0u, 0u, 0u, 0u}, r;
         if (a.x_in) x = *reinterpret_cast<const u32x4 *>(a.x_in + o);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           double s = double(__uint_as_float(x[q]));
 #pragma unroll
-          for (int w = 0; w < W; ++w) s += sums[w][at + uint32_t(q) * kResTile];
+          for (int w = 0; w < W; ++w) s += sums[w][at + uint32_t(q) * kRun];
           r[q] = __float_as_uint(float(s));
         }
         *reinterpret_cast<u32x4 *>(a.x_out + o) = r;
@@ -883,7 +940,7 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
   uint32_t singles = 0;
   int ncover = 0;
   for (int i = 0; i < j.n_iv; ++i) {
-    singles += res_tiles<1>(uint32_t(j.iv[i].n_vec));
+    singles += run_tiles<1>(uint32_t(j.iv[i].n_vec), kResPairLg);
     ncover = std::max(ncover, int(j.iv[i].ncover));
   }
   const ResShape shape =
@@ -892,13 +949,13 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
   for (int i = 0, first = 0; i < j.n_iv; first += j.iv[i].ncover, ++i) {
     const uint32_t n_vec = uint32_t(j.iv[i].n_vec);
     a.part[i] = ResPart{tiles, uint32_t(j.iv[i].vec_begin), n_vec, first, j.iv[i].ncover};
-    tiles += shape.runs == 2 ? res_tiles<2>(n_vec) : res_tiles<1>(n_vec);
+    tiles += shape.runs == 2 ? run_tiles<2>(n_vec, kResPairLg) : run_tiles<1>(n_vec, kResPairLg);
   }
   auto launch = [&](auto waves, auto runs) {
     constexpr int W = decltype(waves)::value, T = decltype(runs)::value;
     // Segments a wave loads before its arithmetic.
     constexpr int U = NS == 1 ? 4 / T : NS == 2 ? (T == 2 && W == 1 ? 1 : 2) : 1;
-    constexpr size_t kOwn = W > 1 ? size_t(W) * T * kResTile * Dec::kVec * sizeof(double) : 0;
+    constexpr size_t kOwn = W > 1 ? size_t(W) * T * kRun * Dec::kVec * sizeof(double) : 0;
     const size_t share = lds_share(g.lds_per_cu, shape.blocks_per_cu);
     const size_t extra = share > kOwn ? share - kOwn : 0;
     hipLaunchKernelGGL((residual_kernel<Dec, NS, W, U, T>), dim3(tiles), dim3(64 * W), extra, s, a);

@@ -82,3 +82,27 @@ def test_ring_tiles(layout, n, m):
             assert _same(other, outs[j])
         cheb.cheb_set_launch_config(**cheb.DEFAULT_LAUNCH_CONFIG)
         cache.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,m", [(3, 1), (2, 2)])
+@pytest.mark.parametrize("extra", [0, 1, 63, 64, 65, 4095, 4096, 4097, 8191])
+def test_pairs_of_runs(dtype, n, m, extra):
+    """Contiguous sources in pairs of runs 4096 vectors apart: whole pairs and
+    every kind of rest behind them, with and without a ragged tail, bit for
+    bit as the 256-lane shape gives it."""
+    vec = 4 if dtype == "f32" else 8
+    numel = (64 * 256 * 512 // (n + m) + extra) * vec + extra % vec
+    g = torch.Generator(device="cuda")
+    g.manual_seed(extra)
+    srcs = [torch.randn(numel, generator=g, device="cuda").to(DT[dtype]) for _ in range(n)]
+    w = np.stack([oracle.weights_row(np.arange(n, dtype=float), n + 0.5 * j) for j in range(m)])
+    outs = [torch.full((numel,), float("nan"), dtype=DT[dtype], device="cuda") for _ in range(m)]
+    say(f"pairs {dtype} n={n} m={m} numel={numel}")
+    cheb.combine_multi(srcs, w, outs)
+    cheb.cheb_set_launch_config(block=256)
+    for j in range(m):
+        other = torch.empty_like(outs[j])
+        cheb.combine(srcs, w[j], other)
+        torch.cuda.synchronize()
+        assert _same(other, outs[j])
