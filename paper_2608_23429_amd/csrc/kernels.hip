@@ -7,22 +7,22 @@
 //    (n+1) x 16 bytes of HBM traffic per 16-byte output vector and 2n flops
 //    per element, far below the fp32 ridge point, so the kernel is laid out
 //    for bandwidth: 128-bit coalesced loads (a wave covers 1 KiB contiguous
-//    per load instruction), all n x unroll loads of a thread issued before
-//    any arithmetic, weights as kernel arguments (they live in SGPRs), fp32
+//    per load instruction), all of a thread's loads issued before any
+//    arithmetic, weights as kernel arguments (they live in SGPRs), fp32
 //    accumulation for bf16 and fp16 storage and fp64 for fp32 storage, and
 //    one hardware round-to-nearest-even pack per element pair
 //    (v_cvt_pk_bf16_f32, v_cvt_pk_f16_f32).  No LDS: nothing is reused
 //    across lanes.
 // 2. The full-step push (Algorithm 1, full computation: store (s, f_s) in
-//    the history): a launch copies up to 64 segments into a slot.
+//    the history): a launch copies up to 64 segments of like size into a
+//    slot.
 // 3. Residual application on a skipped step (Section 3.1, block equation):
 //    the block stack's sum of predicted module outputs added to the
 //    residual stream in one pass.
 // History entries are either contiguous slots or chunk-interleaved lanes
 // (internal.h): vector v of an entry is at (v / 2048) * super + v % 2048
-// from the entry's base, which is v itself when super is 2048.  Every
-// kernel tests that one uniform value and takes the plain 32-bit indexing
-// for contiguous entries.
+// from the entry's base, which is v itself when super is 2048.  One-wave
+// tiles make that place uniform, so it is scalar arithmetic.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -429,10 +429,10 @@ int auto_waves(int ns, int no) {
 }
 
 // Dynamic LDS a block reserves, and never touches, when `blocks` of them are
-// to share a compute unit: an equal share rounded down to the 1280-byte unit LDS is handed out in on
-// gfx950 (a size in between takes the next unit, and one block fewer fits).
-// A share past the 64 KiB a block may have is cut to that, if as many blocks
-// still fit and no more.  Zero when there is no limit or none is possible.
+// to share a compute unit: an equal share rounded down to the 1280-byte unit
+// LDS is handed out in on gfx950 (a size in between takes the next unit, and
+// one block fewer fits).  A share past the 64 KiB a block may have is cut to
+// that, if as many blocks still fit and no more.  Zero when there is no limit or none is possible.
 size_t lds_share(int lds_per_cu, int blocks) {
   constexpr int kMost = 64 << 10;
   if (blocks <= 0 || lds_per_cu <= 0) return 0;
