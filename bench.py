@@ -505,7 +505,7 @@ def device_summary(torch):
     return {"name": p.name, "gcn_arch": getattr(p, "gcnArchName", None),
             "compute_units": p.multi_processor_count,
             "lds_per_cu_bytes": lds if lds >= 0 else None,
-            "lds_reserved_per_64_lane_block_at_7_waves": lds // 7 // 512 * 512
+            "lds_reserved_per_64_lane_block_at_7_waves": lds // 7 // 1280 * 1280
             if lds > 0 else None}
 
 

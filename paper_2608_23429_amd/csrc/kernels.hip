@@ -442,10 +442,10 @@ size_t lds_share(int lds_per_cu, int blocks) {
 }
 
 // The same for the other launch shapes, so that about `waves` waves of the
-// kernel share a compute unit (the LDS is what runs out): an
-// equal share of the compute unit's LDS, rounded down to 512 bytes.  Zero
-// when there is no cap, when the cap is at the hardware's own limit, or when
-// one block would need more than the default 64 KiB of dynamic LDS.
+// kernel share a compute unit (the LDS is what runs out): an equal share of
+// the compute unit's LDS, rounded down to 512 bytes.  Zero when there is no
+// cap, when the cap is at the hardware's own limit, or when one block would
+// need more than the default 64 KiB of dynamic LDS.
 template <int BLK>
 size_t occupancy_lds(const Gpu &g) {
   constexpr int kWavesPerBlock = BLK / 64;
@@ -516,8 +516,9 @@ hipError_t launch_one(const Hist<NS, 1, typename Op::W> &h, uint32_t n_vec, Tail
 }
 
 // Several outputs: one vector per lane, a grid covering the range, 64-lane
-// blocks or 1024-lane blocks for any other configured block, and the non-temporal hint as configured; this keeps the
-// number of kernel instances bounded.
+// blocks or 1024-lane blocks for any other configured block, and the
+// non-temporal hint as configured; this keeps the number of kernel instances
+// bounded.
 template <class Op, int NS, int NO>
 hipError_t launch_many(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, Tail tail,
                        const cheb_launch_config &cfg, const Gpu &dev, hipStream_t s) {
