@@ -601,7 +601,7 @@ struct GatherArgs {
   uint64_t numel[kGatherMax];
 };
 
-// Grid: x = tile of 64 vectors within a segment, y = segment.  Blocks past
+// Grid: x = tile of 64 vectors over a segment, y = segment.  Blocks past
 // their segment's end return at once, so no block searches for its segment;
 // the launcher keeps their number small.  Bound by HBM, half reads and half
 // writes: one-wave blocks at full occupancy mix the two best (FLUX-1024 into
@@ -609,9 +609,12 @@ struct GatherArgs {
 // 500 or more with two or four vectors per lane at any limit on resident
 // blocks; into an interleaved lane 525 against 548).  Source reads and slot
 // writes are streaming (each byte is touched once per push), so both carry
-// the non-temporal hint.  The tile's place in the entry is uniform; a lane
-// past the end of its chunk of an interleaved lane jumps to the next one
-// (contiguous entries have super == kChunkVecs and no jump).
+// the non-temporal hint.  Tiles are whole in the entry, not in the segment (a
+// segment's first one may begin with idle lanes): a tile that straddled
+// 128-byte lines would share them with its neighbours, which run on other
+// XCDs (6 fp32 segments of 41 MB that start anywhere in a line, into one of
+// six lanes: 82 us against 89 with tiles cut from the segment's start).  So
+// a tile lies in one chunk and its place is uniform.
 template <typename E>
 __global__ __launch_bounds__(64) void gather_kernel(GatherArgs a, char *__restrict__ slot,
                                                     uint64_t super) {
@@ -620,17 +623,17 @@ __global__ __launch_bounds__(64) void gather_kernel(GatherArgs a, char *__restri
   const uint64_t numel = a.numel[s];
   const uint32_t n_full = uint32_t(numel / kVec);
   const uint32_t rem = uint32_t(numel % kVec);
+  const uint32_t lead = uint32_t(a.dst_vec[s]) & (kGatherTile - 1);
   const uint32_t first = blockIdx.x * kGatherTile;
   const uint32_t lane = threadIdx.x;
-  if (first > n_full) return;
-  const uint64_t v0 = a.dst_vec[s] + first;
-  const uint32_t r0 = uint32_t(v0) & uint32_t(kChunkVecs - 1);
-  u32x4 *dst = reinterpret_cast<u32x4 *>(slot) + ((v0 >> kChunkShift) * super + r0) + lane +
-               (r0 + lane >= uint32_t(kChunkVecs) ? uint32_t(super - uint64_t(kChunkVecs)) : 0u);
-  const u32x4 *src = static_cast<const u32x4 *>(a.src[s]) + first + lane;
-  if (first + lane < n_full) {
+  if (first > n_full + lead) return;
+  u32x4 *dst = reinterpret_cast<u32x4 *>(slot) +
+               lane_vec(a.dst_vec[s] - lead + first, super) + lane;
+  const uint32_t i = first + lane - lead;  // wraps to past any segment before its first vector
+  const u32x4 *src = static_cast<const u32x4 *>(a.src[s]) + i;
+  if (i < n_full) {
     store16<true>(dst, load16<true>(src));
-  } else if (first + lane == n_full && rem != 0) {
+  } else if (i == n_full && rem != 0) {
     // Last, partial vector: copy the remaining elements one by one and zero
     // the padding up to the 16-byte boundary.
     const E *src_e = reinterpret_cast<const E *>(src);
@@ -1049,12 +1052,15 @@ int launch_gather(int dtype, void *slot_base, const GatherSeg *segs, int n_segs,
     for (; at < order.size() && used < kGatherMax; ++at, ++used) {
       const GatherSeg &g = *order[at];
       const uint64_t vecs = (uint64_t(g.numel) + uint64_t(vec) - 1) / uint64_t(vec);
-      const uint64_t tiles = (vecs + kGatherTile - 1) / kGatherTile;
-      if (used == 0) most = tiles;
-      idle += most - tiles;
-      if (idle > kIdleBlocks) break;
+      const uint64_t first = uint64_t(g.dst_offset) / uint64_t(vec);
+      const uint64_t tiles = (first % kGatherTile + vecs + kGatherTile - 1) / kGatherTile;
+      const uint64_t wide = std::max(most, tiles);
+      const uint64_t more = uint64_t(used) * (wide - most) + (wide - tiles);
+      if (idle + more > kIdleBlocks) break;
+      most = wide;
+      idle += more;
       a.src[used] = g.src;
-      a.dst_vec[used] = uint64_t(g.dst_offset) / uint64_t(vec);
+      a.dst_vec[used] = first;
       a.numel[used] = uint64_t(g.numel);
     }
     char *slot = static_cast<char *>(slot_base);

@@ -1,6 +1,6 @@
 """The push's 64-vector tiles: segments around a tile's end, ragged and empty
-ones, very unlike sizes (several launches, largest first) and more segments
-than one launch takes, read back bit for bit with zeroed padding."""
+ones, very unlike sizes (several launches, largest first), equal ones that
+start anywhere in a tile, and more segments than one launch takes, read back bit for bit with zeroed padding."""
 import pytest
 import torch
 
@@ -14,6 +14,7 @@ SIZES = {
     "tile_edges": [1, 7, 8, 9, 511, 512, 513, 519, 520, 521, 1023, 1024, 1025],
     "empty": [0, 512, 0, 3, 0],
     "unlike": [5, 16385 * 512, 3, 16385 * 512 + 9, 700, 16000 * 512, 8],
+    "alike_shifted": [528] * 70,               # tiles per segment vary with its place
     "many": [(j * 37) % 2000 for j in range(150)],
 }
 
