@@ -29,7 +29,8 @@ if ROOT not in sys.path:
 
 METRIC = "achieved HBM GB/s and µs per skipped step, FLUX-1024 cache shape, 1 MI355X"
 PEAK_HBM_GBPS = 8000.0
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2608_23429_amd", "csrc", "kernels.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2608_23429_amd", "csrc", f)
+                  for f in ("kernels.hip", "tiles.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 CEILING_LIB = os.path.join(ROOT, "bench_ceiling.so")
 LAYOUT = "interleaved"
@@ -40,8 +41,11 @@ def log(msg):
 
 
 def kernel_sha256():
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    sha = hashlib.sha256()
+    for path in KERNEL_SOURCES:
+        with open(path, "rb") as f:
+            sha.update(f.read())
+    return sha.hexdigest()
 
 
 def measured_traffic(workload):
