@@ -764,7 +764,7 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int e = 0; e < V; ++e) acc[i][e] = 0.0;
+    for (int e = 0; e < V; ++e) acc[i][e] = -0.0;  // the sum of nothing: x + -0.0 is x, -0.0 too
   u32x4 x1[W == 1 ? T * V / 4 : 1];  // one wave: the residual's own values, ahead of the history
   if constexpr (W == 1) {
 #pragma unroll

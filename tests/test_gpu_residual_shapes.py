@@ -96,3 +96,25 @@ def test_intervals(layout, n_intervals):
             off.append(unit * i)
     for x in (True, False):
         _check("bf16", 3, seg, off, res_n, layout, x, n_intervals)
+
+
+@pytest.mark.parametrize("layout", ["slots", "interleaved"])
+@pytest.mark.parametrize("ncover", [1, 3, 5, 17])
+def test_zeros_keep_their_sign(layout, ncover):
+    """A sum that starts from the residual itself: elements that no segment
+    covers come out bit for bit (both zeros, infinities, subnormals), and a
+    negative zero plus terms of negative zero stays one.  Exact."""
+    half = 8 * 65
+    x_in = torch.tensor([-0.0, 0.0, 1e-42, -1e-42, float("inf"), -float("inf"), -3.5, 7.25],
+                        device="cuda").repeat(2 * half // 8)
+    x_in[:half] = -0.0
+    cache = cheb.ChebCache(2, torch.bfloat16, [half] * ncover, layout=layout)
+    for k in range(2):
+        cache.push(float(k), [torch.full((half,), -0.0, dtype=torch.bfloat16, device="cuda")] *
+                   ncover)
+    say(f"residual zeros {layout} segs={ncover}")
+    for x in (x_in, None):
+        out = cache.residual_apply([0.5, 2.0], [0] * ncover, torch.empty_like(x_in), x)
+        want = torch.zeros_like(x_in) if x is None else x_in
+        assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+    cache.close()
