@@ -54,3 +54,28 @@ def test_fp64_pointers_and_results():
     x.flags.writeable = False
     want = B.cheb_precompute_weights([0.0, 1.0, 2.0], [3.0])
     assert np.array_equal(B.cheb_precompute_weights(x, np.array([3.0, 9.0])[::2]), want)
+
+
+class _Writes:
+    """Stands for the library: every call succeeds and fills the weights."""
+
+    def __getattr__(self, name):
+        def call(*args):
+            rows = args[-1]
+            for i in range(len(rows)):
+                rows[i] = float(i)
+            return B.CHEB_OK
+        return call
+
+
+@pytest.mark.parametrize("n_slots", [0, 1, B.CHEB_MAX_SLOTS, B.CHEB_MAX_SLOTS + 1, 40])
+def test_weights_clipped_to_what_the_library_holds(monkeypatch, n_slots):
+    """A history size past the largest gives what is there, not an error after
+    the launch has gone out."""
+    monkeypatch.setattr(B, "LIB", _Writes())
+    most = np.arange(float(B.CHEB_MAX_SLOTS * B.CHEB_MAX_OUTPUTS))
+    assert np.array_equal(B.cheb_extrapolate_at(0, 0.5, 0, n_slots=n_slots),
+                          most[:min(n_slots, B.CHEB_MAX_SLOTS)])
+    if n_slots <= B.CHEB_MAX_SLOTS + 1:        # the rows are packed
+        assert np.array_equal(B.cheb_extrapolate_at_multi(0, [0.5, 0.6], [0, 0], n_slots=n_slots),
+                              most[:2 * n_slots].reshape(2, n_slots))
