@@ -30,7 +30,7 @@ if ROOT not in sys.path:
 METRIC = "achieved HBM GB/s and µs per skipped step, FLUX-1024 cache shape, 1 MI355X"
 PEAK_HBM_GBPS = 8000.0
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2608_23429_amd", "csrc", f)
-                  for f in ("kernels.hip", "tiles.h")]
+                  for f in ("kernels.hip", "shapes.h", "tiles.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 CEILING_LIB = os.path.join(ROOT, "bench_ceiling.so")
 LAYOUT = "interleaved"

@@ -105,8 +105,7 @@ int launch_residual(int dtype, int n, const uint64_t *base, const double *w,
 
 // The same for several intervals in one launch: interval i adds the next
 // iv[i].ncover offsets of the table of n_delta.  n_iv <= kMaxResIntervals,
-// n_delta <= residual_max_cover(), every n_vec > 0, all tiles of 64 vectors
-// below 2^31.
+// n_delta <= residual_max_cover(), every n_vec > 0, vector indices below 2^31.
 struct ResidualInterval {
   int64_t vec_begin, n_vec;
   int32_t ncover;

@@ -1,0 +1,37 @@
+// The residual kernel's launch shapes, on the CPU: over every history size,
+// storage type, layout and number of covering segments, and sizes up to the
+// last one a residual may have, the grid stays within HIP's 2^32 - 1 threads.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include "shapes.h"
+#include "tiles.h"
+
+using namespace cheb;
+
+static void check_grid(int ns, int vec, int ncover, uint32_t n_vec, bool contiguous) {
+  const uint32_t singles = run_tiles<1>(n_vec, kRunLg);
+  const ResShape s =
+      within_grid(residual_shape(ns, vec, ncover, singles, contiguous, 256), singles);
+  const uint64_t tiles = s.runs == 2 ? run_tiles<2>(n_vec, 12) : singles;
+  const uint64_t threads = tiles * 64u * uint64_t(s.waves);
+  if (s.waves < 1 || s.blocks_per_cu < 0 || threads == 0 || threads > UINT32_MAX) {
+    fprintf(stderr, "%d entries, %d segments, %u vectors of %d: %d waves, %llu threads\n", ns,
+            ncover, n_vec, vec, s.waves, (unsigned long long)threads);
+    exit(1);
+  }
+}
+
+int main() {
+  const uint32_t sizes[] = {1, 64, 65, 1u << 14, 1u << 20, 1u << 25, (1u << 28) - 64, 1u << 28,
+                            1u << 29, (1u << 30) - 64, (1u << 30) - 1, 1u << 30,
+                            (1u << 30) + 1, (1u << 31) - 65, (1u << 31) - 1};
+  for (int ns = 1; ns <= 8; ++ns)
+    for (int vec = 4; vec <= 8; vec += 4)
+      for (int ncover = 0; ncover <= 128; ++ncover)
+        for (uint32_t n_vec : sizes)
+          for (int contiguous = 0; contiguous < 2; ++contiguous)
+            check_grid(ns, vec, ncover, n_vec, contiguous != 0);
+  printf("shapes ok\n");
+  return 0;
+}
