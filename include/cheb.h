@@ -546,7 +546,10 @@ CHEB_API int cheb_residual_reduce(const void *const *seg_src, const int64_t *seg
  *                applies only where that share is at most 64 KiB (64- and
  *                256-thread blocks) and is ignored otherwise.  While a
  *                prediction runs, kernels on other streams find that LDS
- *                taken; -1 leaves it free.
+ *                taken; -1 leaves it free.  The residual calls reserve LDS in
+ *                the same way, up to all of it, under limits of their own;
+ *                -1 leaves them only what their sums take (at most 64 KiB a
+ *                block), other values do not reach them.
  * Default {64, 1, 1, 0, 0}.  On MI355X a bf16 history of 5-6 entries
  * streams at 0.83 (contiguous) to 0.87 (interleaved) of the HBM peak under
  * the chosen cap, against 0.75 with 1024-thread blocks at full occupancy:

@@ -335,7 +335,8 @@ __global__ __launch_bounds__(BLK) void combine_kernel(Hist<NS, NO, typename Op::
 struct Gpu {
   int cus;         // compute units
   int lds_per_cu;  // LDS bytes per compute unit
-  int waves;       // occupancy cap in waves per compute unit, 0: none
+  int waves;       // occupancy cap in waves per compute unit, 0: none (of the
+                   // residual kernel: as configured, and only -1 counts)
 };
 
 // Runs per tile, the distance between them and how many one-wave blocks share
@@ -869,8 +870,7 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
     // Segments a wave loads before its arithmetic.
     constexpr int U = NS == 1 ? 4 / T : NS == 2 ? (T == 2 && W == 1 ? 1 : 2) : 1;
     constexpr size_t kOwn = W > 1 ? size_t(W) * T * kRun * Dec::kVec * sizeof(double) : 0;
-    const size_t share = lds_share(g.lds_per_cu, shape.blocks_per_cu);
-    const size_t extra = share > kOwn ? share - kOwn : 0;
+    const size_t extra = residual_lds(g.lds_per_cu, shape.blocks_per_cu, kOwn, g.waves);
     hipLaunchKernelGGL((residual_kernel<Dec, NS, W, U, T>), dim3(tiles), dim3(64 * W), extra, s, a);
   };
   const std::integral_constant<int, 1> one;
@@ -998,6 +998,7 @@ int launch_residual_intervals(int dtype, int n, const uint64_t *base, const doub
   Gpu g{0, 0, 0};
   int rc = device_info(&g.cus, &g.lds_per_cu);
   if (rc != CHEB_OK) return rc;
+  g.waves = launch_shape().waves_per_cu;
   const ResJob j{base, w, delta, n_delta, iv, n_iv, x_in, x_out, uint64_t(super_vecs)};
   hipError_t e;
   switch (dtype) {

@@ -77,6 +77,14 @@ inline ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, bool
   return {4, ncover >= 24 ? std::max(2, 4 - ns / 2) : 4};
 }
 
+// LDS reserved on top of a block's own so that `blocks` of them share a compute
+// unit.  None where the caller wants the LDS left free (waves_per_cu -1 of the
+// launch shape): 1 to 4% slower, but kernels on other streams find it.
+inline size_t residual_lds(int lds_per_cu, int blocks, size_t own, int waves_per_cu) {
+  const size_t share = waves_per_cu < 0 ? 0 : lds_share(lds_per_cu, blocks);
+  return share > own ? share - own : 0;
+}
+
 // The same shape for a launch of that many tiles of one run (half as many of
 // two).  HIP refuses a grid of 2^32 threads or more, which 4 waves a tile of
 // 64 vectors reach at 2^30 vectors, 8 waves at 2^29; from there on, one wave a

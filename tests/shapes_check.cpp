@@ -1,6 +1,9 @@
 // The residual kernel's launch shapes, on the CPU: over every history size,
 // storage type, layout and number of covering segments, and sizes up to the
 // last one a residual may have, the grid stays within HIP's 2^32 - 1 threads.
+// Reserved LDS lets as many blocks onto a compute unit as wanted and (to 12, where
+// the unit it is handed out in still tells them apart) no more, and none is
+// reserved where the caller wants it free.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -22,7 +25,24 @@ static void check_grid(int ns, int vec, int ncover, uint32_t n_vec, bool contigu
   }
 }
 
+static void check_lds() {
+  constexpr int kCu = 160 << 10, kUnit = 1280;   // handed out in whole units
+  for (int blocks = 0; blocks <= 32; ++blocks)
+    for (size_t own = 0; own <= 64u << 10; own += 512) {
+      const size_t extra = residual_lds(kCu, blocks, own, 0), all = own + extra;
+      const size_t taken = (all + kUnit - 1) / kUnit * kUnit;
+      const bool fits = extra == 0 || (all <= 64u << 10 && taken * blocks <= size_t(kCu) &&
+                                       (blocks > 12 || taken * (blocks + 1) > size_t(kCu)));
+      if (!fits || residual_lds(kCu, blocks, own, -1) != 0 ||
+          residual_lds(kCu, blocks, own, 7) != extra) {
+        fprintf(stderr, "%d blocks, own LDS %zu: %zu reserved\n", blocks, own, extra);
+        exit(1);
+      }
+    }
+}
+
 int main() {
+  check_lds();
   const uint32_t sizes[] = {1, 64, 65, 1u << 14, 1u << 20, 1u << 25, (1u << 28) - 64, 1u << 28,
                             1u << 29, (1u << 30) - 64, (1u << 30) - 1, 1u << 30,
                             (1u << 30) + 1, (1u << 31) - 65, (1u << 31) - 1};
