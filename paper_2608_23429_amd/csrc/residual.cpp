@@ -15,24 +15,6 @@
 
 using namespace cheb;
 
-namespace cheb {
-
-// A build of the host sources without the device code links only
-// launch_residual; the library's own definition replaces this one.
-__attribute__((weak)) int launch_residual_intervals(
-    int dtype, int n, const uint64_t *base, const double *w, const int64_t *delta, int,
-    const ResidualInterval *iv, int n_iv, const float *x_in, float *x_out, int64_t super_vecs,
-    hipStream_t stream) {
-  for (int i = 0; i < n_iv; delta += iv[i].ncover, ++i) {
-    int rc = launch_residual(dtype, n, base, w, delta, iv[i].ncover, x_in, x_out,
-                             iv[i].vec_begin, iv[i].n_vec, super_vecs, stream);
-    if (rc != CHEB_OK) return rc;
-  }
-  return ok();
-}
-
-}  // namespace cheb
-
 namespace {
 
 struct Interval {
@@ -90,9 +72,9 @@ int check_residual_buffers(const float *x_in, float *x_out, int64_t res_numel) {
 }
 
 // Runs the plan.  When every interval's covering segments fit one launch's
-// tables, it is one launch, the largest interval first, so that the chip
-// does not run empty between them.  Otherwise, per interval, the covering segments in chunks of the
-// table's size; the first chunk reads x_in, later ones x_out.
+// tables, it is one launch, the largest interval first, so that the chip does
+// not run empty between them.  Otherwise, per interval, the covering segments
+// in chunks of the table's size; the first chunk reads x_in, later ones x_out.
 template <class DeltaFn>
 int run(int dtype, int n, const uint64_t *base, const double *w,
         const std::vector<Interval> &plan_iv, DeltaFn delta_of, const float *x_in, float *x_out,

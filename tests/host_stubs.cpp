@@ -1,7 +1,9 @@
 // Stand-ins for the device launchers of libcheb, for a host-only build of
 // the library's C++ sources under AddressSanitizer / UBSan / ThreadSanitizer.
-// Prediction and residual launches always report an error (the host test
-// programs never reach one with valid arguments).  The segment-copy launcher
+// Prediction launches always report an error (the host test programs never
+// reach one with valid arguments), and so do residual launches until
+// stub_residual_on_host(1): then the tables are checked and fp32 entries in
+// host memory are added up as they say.  The segment-copy launcher
 // models the real one's batches of 64 segments: a budget set by
 // stub_gather_batches_ok() says how many batches succeed before one fails,
 // so a push that fails part-way through its launches can be tested on the
@@ -12,9 +14,12 @@
 
 namespace {
 std::atomic<int> g_gather_batches_ok{0};
+std::atomic<int> g_residual_on_host{0}, g_residual_launches{0};
 }
 
 extern "C" void stub_gather_batches_ok(int n) { g_gather_batches_ok.store(n); }
+extern "C" void stub_residual_on_host(int on) { g_residual_on_host.store(on); }
+extern "C" int stub_residual_launches() { return g_residual_launches.load(); }
 
 namespace cheb {
 
@@ -35,9 +40,47 @@ int launch_gather(int, void *, const GatherSeg *, int n_segs, int64_t, hipStream
 
 int residual_max_cover() { return 128; }
 
-int launch_residual(int, int, const uint64_t *, const double *, const int64_t *, int,
-                    const float *, float *, int64_t, int64_t, int64_t, hipStream_t) {
-  return fail(CHEB_E_HIP, "host-only build: no device launch");
+int launch_residual_intervals(int dtype, int n, const uint64_t *base, const double *w,
+                              const int64_t *delta, int n_delta, const ResidualInterval *iv,
+                              int n_iv, const float *x_in, float *x_out, int64_t super_vecs,
+                              hipStream_t) {
+  if (!g_residual_on_host.load()) return fail(CHEB_E_HIP, "host-only build: no device launch");
+  int covers = 0;
+  for (int i = 0; i < n_iv; ++i) {
+    if (iv[i].vec_begin < 0 || iv[i].n_vec <= 0 || iv[i].ncover < 0)
+      return fail(CHEB_E_INVAL, "residual interval %d is malformed", i);
+    for (int h = 0; h < i; ++h)
+      if (iv[i].vec_begin < iv[h].vec_begin + iv[h].n_vec &&
+          iv[h].vec_begin < iv[i].vec_begin + iv[i].n_vec)
+        return fail(CHEB_E_INVAL, "residual intervals %d and %d overlap", h, i);
+    covers += iv[i].ncover;
+  }
+  if (dtype != CHEB_F32 || n_iv < 1 || n_iv > kMaxResIntervals || covers != n_delta ||
+      n_delta > residual_max_cover())
+    return fail(CHEB_E_INVAL, "residual tables are malformed");
+  for (int i = 0; i < n_iv; delta += iv[i].ncover, ++i)
+    for (int64_t j = iv[i].vec_begin; j < iv[i].vec_begin + iv[i].n_vec; ++j)
+      for (int e = 0; e < 4; ++e) {
+        double sum = x_in ? double(x_in[4 * j + e]) : 0.0;
+        for (int c = 0; c < iv[i].ncover; ++c)
+          for (int k = 0; k < n; ++k) {
+            const int64_t v = delta[c] + j;
+            const uint64_t at =
+                base[k] + 16u * uint64_t(v / kChunkVecs * super_vecs + v % kChunkVecs);
+            sum += w[k] * double(reinterpret_cast<const float *>(at)[e]);
+          }
+        x_out[4 * j + e] = float(sum);
+      }
+  g_residual_launches.fetch_add(1);
+  return ok();
+}
+
+int launch_residual(int dtype, int n, const uint64_t *base, const double *w, const int64_t *delta,
+                    int ncover, const float *x_in, float *x_out, int64_t vec_begin,
+                    int64_t n_vec, int64_t super_vecs, hipStream_t stream) {
+  const ResidualInterval iv{vec_begin, n_vec, ncover};
+  return launch_residual_intervals(dtype, n, base, w, delta, ncover, &iv, 1, x_in, x_out,
+                                   super_vecs, stream);
 }
 
 }  // namespace cheb

@@ -95,3 +95,29 @@ def test_failed_push_leaves_no_half_written_entry(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "push failure ok" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_residual_plan(tmp_path):
+    """The intervals, offsets and tables of residual calls, added up on the
+    host by the stub launcher, give the plain sum over the segments.  Under
+    ASan and UBSan, CPU only."""
+    san = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+           "-fno-omit-frame-pointer", "-g", "-O1"]
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", os.path.join(ROCM, "include")]
+    objs = []
+    for src in HOST_SOURCES + ["host_stubs.cpp", "residual_plan_check.cpp"]:
+        path = os.path.join(CSRC if src in HOST_SOURCES else HERE, src)
+        obj = os.path.join(tmp_path, src + ".o")
+        subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", *san, *inc, "-c", path,
+                        "-o", obj], check=True)
+        objs.append(obj)
+    exe = os.path.join(tmp_path, "residual_plan_check")
+    libdir = os.path.join(ROCM, "lib")
+    subprocess.run(["g++", *san, *objs, "-o", exe, "-L", libdir, "-lamdhip64",
+                    f"-Wl,-rpath,{libdir}", "-lm"], check=True)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=1",
+               UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1")
+    r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert "residual plan ok" in r.stdout
