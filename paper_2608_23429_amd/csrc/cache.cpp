@@ -5,6 +5,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -153,6 +154,45 @@ int cache_view(const cheb_cache *c, CacheView *v) {
   v->arena = c->arena;
   v->arena_bytes = c->arena_bytes;
   return CHEB_OK;
+}
+
+int order_segments(GatherSeg *segs, int n) {
+  int held = 0;
+  bool alike = true;
+  for (int j = 0; j < n; ++j) {
+    if (segs[j].numel == 0) continue;  // nothing to copy
+    segs[held++] = segs[j];
+    alike = alike && segs[held - 1].numel == segs[0].numel;
+  }
+  if (!alike)
+    std::sort(segs, segs + held, [](const GatherSeg &x, const GatherSeg &y) {
+      return x.numel > y.numel || (x.numel == y.numel && x.dst_offset < y.dst_offset);
+    });
+  return held;
+}
+
+// Segments go in launches of up to 64 whose sizes are alike: a launch's grid
+// is as wide as its largest segment, and every block past the end of a
+// smaller one still costs its dispatch (about 4.7 blocks a nanosecond on
+// MI355X).  A launch is closed before the blocks without work would pass
+// 16384, about what another launch costs (FLUX-1024: three launches with 15K
+// idle blocks of 1.6M in place of two with 525K of 2.1M).
+int next_gather(const GatherSeg *segs, int n, int64_t vec, uint32_t *tiles) {
+  constexpr int64_t kIdleBlocks = 16384;
+  int64_t most = 0, idle = 0;
+  int used = 0;
+  for (; used < n && used < kGatherSegs; ++used) {
+    const int64_t vecs = (segs[used].numel + vec - 1) / vec;
+    const int64_t first = segs[used].dst_offset / vec;
+    const int64_t own = (first % kGatherTileVecs + vecs + kGatherTileVecs - 1) / kGatherTileVecs;
+    const int64_t wide = std::max(most, own);
+    const int64_t more = used * (wide - most) + (wide - own);
+    if (idle + more > kIdleBlocks) break;
+    most = wide;
+    idle += more;
+  }
+  *tiles = uint32_t(most);
+  return used;
 }
 
 }  // namespace cheb

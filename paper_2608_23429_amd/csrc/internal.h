@@ -71,14 +71,24 @@ int extrapolate_newest(cheb_cache *c, int32_t used, const double *w, int32_t n_o
                        void *const *out, void *stream);
 
 // Segment copy into one slot; zero-fills each segment's padding up to the
-// next 16-byte boundary.
+// next 16-byte boundary.  Reorders `segs`.
 struct GatherSeg {
   const void *src;     // device, 16-byte aligned
   int64_t dst_offset;  // elements from the slot base (16-byte multiple)
   int64_t numel;       // elements to copy
 };
-int launch_gather(int dtype, void *slot_base, const GatherSeg *segs, int n_segs,
-                  int64_t super_vecs, hipStream_t stream);
+int launch_gather(int dtype, void *slot_base, GatherSeg *segs, int n_segs, int64_t super_vecs,
+                  hipStream_t stream);
+
+// The launches of a segment copy (cache.cpp).  order_segments() puts the
+// segments that are not empty in front, larger ones first, and returns their
+// number; next_gather() says how many of the first of them the next launch
+// takes (at least one) and how many tiles of kGatherTileVecs 16-byte vectors
+// its largest has.
+constexpr int kGatherSegs = 64;
+constexpr int64_t kGatherTileVecs = 64;
+int order_segments(GatherSeg *segs, int n);
+int next_gather(const GatherSeg *segs, int n, int64_t vec, uint32_t *tiles);
 
 // Read-only view of a cache's layout and ring state (cache.cpp).
 struct CacheView {

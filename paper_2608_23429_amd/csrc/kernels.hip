@@ -30,7 +30,6 @@
 
 #include <algorithm>
 #include <type_traits>
-#include <vector>
 
 #include "internal.h"
 #include "shapes.h"
@@ -565,7 +564,7 @@ struct GatherArgs {
 
 // Grid: x = tile of 64 vectors over a segment, y = segment.  Blocks past
 // their segment's end return at once, so no block searches for its segment;
-// the launcher keeps their number small.  Bound by HBM, half reads and half
+// the launches are planned with few of them (next_gather).  Bound by HBM, half reads and half
 // writes: one-wave blocks at full occupancy mix the two best (FLUX-1024 into
 // a contiguous slot: 487 us, 6.6 TB/s, against 514 with 256-lane blocks and
 // 500 or more with two or four vectors per lane at any limit on resident
@@ -930,50 +929,25 @@ int launch_combine(int dtype, const void *const *src, int n, const double *w, in
   return ok();
 }
 
-// Segments go in launches of up to 64 whose sizes are alike: a launch's grid
-// is as wide as its largest segment, and every block past the end of a
-// smaller one still costs its dispatch (about 4.7 blocks a nanosecond on
-// MI355X).  A launch is closed, largest segments first, before the blocks
-// without work would pass 16384, about what another launch costs (FLUX-1024:
-// three launches with 15K idle blocks of 1.6M in place of two with 525K of
-// 2.1M).
-int launch_gather(int dtype, void *slot_base, const GatherSeg *segs, int n_segs,
-                  int64_t super_vecs, hipStream_t stream) {
-  constexpr uint64_t kIdleBlocks = 16384;
-  const int vec = elems_per_vec(dtype);
-  std::vector<const GatherSeg *> order;
-  order.reserve(size_t(n_segs));
-  bool alike = true;
-  for (int j = 0; j < n_segs; ++j) {
-    if (segs[j].numel == 0) continue;  // nothing to copy
-    order.push_back(&segs[j]);
-    alike = alike && segs[j].numel == order[0]->numel;
-  }
-  if (!alike)
-    std::sort(order.begin(), order.end(), [](const GatherSeg *x, const GatherSeg *y) {
-      return x->numel > y->numel || (x->numel == y->numel && x->dst_offset < y->dst_offset);
-    });
+int launch_gather(int dtype, void *slot_base, GatherSeg *segs, int n_segs, int64_t super_vecs,
+                  hipStream_t stream) {
+  static_assert(kGatherMax == kGatherSegs && int64_t(kGatherTile) == kGatherTileVecs,
+                "the tables and tiles that the launches are planned for");
+  n_segs = order_segments(segs, n_segs);
+  const int64_t vec = elems_per_vec(dtype);
   GatherArgs a;
-  for (size_t at = 0; at < order.size();) {
+  for (int at = 0, used = 0; at < n_segs; at += used) {
+    uint32_t tiles = 0;
+    used = next_gather(segs + at, n_segs - at, vec, &tiles);
     memset(&a, 0, sizeof a);
-    uint64_t most = 0, idle = 0;
-    int used = 0;
-    for (; at < order.size() && used < kGatherMax; ++at, ++used) {
-      const GatherSeg &g = *order[at];
-      const uint64_t vecs = (uint64_t(g.numel) + uint64_t(vec) - 1) / uint64_t(vec);
-      const uint64_t first = uint64_t(g.dst_offset) / uint64_t(vec);
-      const uint64_t tiles = (first % kGatherTile + vecs + kGatherTile - 1) / kGatherTile;
-      const uint64_t wide = std::max(most, tiles);
-      const uint64_t more = uint64_t(used) * (wide - most) + (wide - tiles);
-      if (idle + more > kIdleBlocks) break;
-      most = wide;
-      idle += more;
-      a.src[used] = g.src;
-      a.dst_vec[used] = first;
-      a.numel[used] = uint64_t(g.numel);
+    for (int j = 0; j < used; ++j) {
+      const GatherSeg &g = segs[at + j];
+      a.src[j] = g.src;
+      a.dst_vec[j] = uint64_t(g.dst_offset / vec);
+      a.numel[j] = uint64_t(g.numel);
     }
     char *slot = static_cast<char *>(slot_base);
-    const dim3 grid{static_cast<uint32_t>(most), static_cast<uint32_t>(used), 1u};
+    const dim3 grid{tiles, static_cast<uint32_t>(used), 1u};
     const uint64_t sv = uint64_t(super_vecs);
     if (elem_bytes(dtype) == 2)
       hipLaunchKernelGGL(gather_kernel<uint16_t>, grid, dim3(kGatherTile), 0, stream, a, slot, sv);
@@ -984,10 +958,6 @@ int launch_gather(int dtype, void *slot_base, const GatherSeg *segs, int n_segs,
   }
   return ok();
 }
-
-}  // namespace cheb
-
-namespace cheb {
 
 int residual_max_cover() { return kResCover; }
 

@@ -4,10 +4,11 @@
 // reach one with valid arguments), and so do residual launches until
 // stub_residual_on_host(1): then the tables are checked and fp32 entries in
 // host memory are added up as they say.  The segment-copy launcher
-// models the real one's batches of 64 segments: a budget set by
-// stub_gather_batches_ok() says how many batches succeed before one fails,
-// so a push that fails part-way through its launches can be tested on the
-// CPU.  The budget starts at 0 (every copy fails).
+// goes through the real one's launches, planned by the same functions: a
+// budget set by stub_gather_batches_ok() says how many succeed before one
+// fails, so a push that fails part-way through them can be tested on the CPU.
+// The budget starts at 0 (every copy fails).  Each launch must take 1 to 64
+// segments, cover them with its tiles and leave few of those without work.
 #include <atomic>
 
 #include "internal.h"
@@ -28,11 +29,27 @@ int launch_combine(int, const void *const *, int, const double *, int, void *con
   return fail(CHEB_E_HIP, "host-only build: no device launch");
 }
 
-int launch_gather(int, void *, const GatherSeg *, int n_segs, int64_t, hipStream_t) {
-  for (int first = 0; first < n_segs; first += 64) {
+int launch_gather(int dtype, void *, GatherSeg *segs, int n_segs, int64_t, hipStream_t) {
+  const int vec = elems_per_vec(dtype);
+  n_segs = order_segments(segs, n_segs);
+  for (int at = 0, used = 0, launch = 0; at < n_segs; at += used, ++launch) {
+    uint32_t tiles = 0;
+    used = next_gather(segs + at, n_segs - at, vec, &tiles);
+    int64_t idle = 0;
+    for (int j = at; j < at + used; ++j) {
+      const int64_t first = segs[j].dst_offset / vec % kGatherTileVecs;
+      const int64_t end = first + (segs[j].numel + vec - 1) / vec;
+      const int64_t left = int64_t(tiles) - (end + kGatherTileVecs - 1) / kGatherTileVecs;
+      if (segs[j].numel <= 0 || left < 0)
+        return fail(CHEB_E_INVAL, "copy launch %d does not cover segment %d", launch, j);
+      idle += left;
+    }
+    if (used < 1 || used > kGatherSegs || idle > 16384)
+      return fail(CHEB_E_INVAL, "copy launch %d of %d segments, %lld idle tiles", launch, used,
+                  (long long)idle);
     if (g_gather_batches_ok.fetch_sub(1) <= 0) {
       g_gather_batches_ok.store(0);
-      return fail(CHEB_E_HIP, "host-only build: copy launch %d refused", first / 64);
+      return fail(CHEB_E_HIP, "host-only build: copy launch %d refused", launch);
     }
   }
   return ok();
