@@ -338,61 +338,6 @@ struct Gpu {
                    // residual kernel: as configured, and only -1 counts)
 };
 
-// Runs per tile, the distance between them and how many one-wave blocks share
-// a compute unit (0: no limit), from the history size, the number of outputs,
-// the layout and the work.  Too few blocks leave the memory latency uncovered,
-// too many flood the memory queues and slow the writes.  Measured on MI355X,
-// bf16, entries of 0.1 to 1.6 GB, single runs within 3% of the best of 5 to
-// 25 blocks and none:
-//  - one output: about 40 KiB of loads in flight from interleaved entries, 45
-//    to 48 from contiguous ones (6 interleaved entries of 1.6 GB: 1627 us with
-//    7, 1642 with 6, over 1670 with 8; 5 contiguous ones: 1417 us with 9, 1447
-//    with 10);
-//  - several outputs: about 60 KiB of loads and stores (2 entries, 5 outputs
-//    of 264 MB: 291 us with 9, 299 with 12, 319 without a limit), and not
-//    below 6 to 8;
-//  - a call of under 512 KiB a compute unit is over before the queues fill
-//    and wants twice as many (6 entries of 9 MB: 11.4 us with 16, 12.6 with
-//    7);
-//  - above that, contiguous entries in tiles of two runs 64 KiB apart, which
-//    share DRAM rows, for several outputs and for one output of 3 to 5
-//    entries (2 entries, 5 outputs of 264 MB: 289 us -> 282; 6 entries, 3
-//    outputs of 1.06 GB in fp16: 1452 -> 1434; 3 entries of 264 MB 159 -> 154;
-//    5 of 528 MB 473 -> 467).  One output of 6 entries or more loses 2% by it,
-//    interleaved entries gain nothing, and one or two entries 1%.
-struct StreamShape {
-  int blocks_per_cu;  // 0: no limit
-  int runs = 1;
-  uint32_t lg = kRunLg;  // of the vectors from run to run
-};
-
-bool large_call(int ns, int no, uint32_t n_vec, int cus) {
-  return uint64_t(n_vec / kRun) * uint64_t(ns + no) >= 512u * uint64_t(cus);
-}
-
-// Blocks of single runs.
-int single_blocks(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
-  static constexpr int kOne[2][CHEB_MAX_SLOTS + 1] = {{0, 0, 0, 16, 11, 9, 8, 7, 6},
-                                                      {0, 0, 0, 14, 9, 8, 7, 6, 5}};
-  const int sum = ns + no;
-  int blocks = kOne[interleaved][ns];
-  if (no > 1) {
-    const int least = sum >= 12 ? 6 : sum <= 9 && !interleaved ? 8 : 7;
-    blocks = std::max(least, (60 + sum / 2) / sum);
-  }
-  return large_call(ns, no, n_vec, cus) ? blocks : 2 * blocks;
-}
-
-StreamShape stream_shape(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
-  if (large_call(ns, no, n_vec, cus)) {
-    const int sum = ns + no;
-    if (!interleaved && no > 1)
-      return {std::max(sum >= 14 ? 4 : 5, (36 + sum / 2) / sum), 2, 12};
-    if (!interleaved && ns >= 3 && ns <= 5) return {(28 + sum / 2) / sum, 2, 12};
-  }
-  return {single_blocks(ns, no, interleaved, n_vec, cus)};
-}
-
 // Waves per compute unit of the other launch shapes, whose loops and larger
 // blocks came out best at 44 KiB of loads in flight (one output) and 36
 // (several).
@@ -447,8 +392,10 @@ hipError_t launch_stream(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, 
     if (cfg.waves_per_cu == 0) {
       const StreamShape shape =
           stream_shape(NS, NO, h.super != uint64_t(kChunkVecs), n_vec, g.cus);
-      if (shape.runs == 2)
-        return launch_runs<Op, NS, NO, 2, NT>(h, n_vec, tail, shape.blocks_per_cu, shape.lg, g, s);
+      if constexpr (takes_pairs(NS, NO))
+        if (shape.runs == 2)
+          return launch_runs<Op, NS, NO, 2, NT>(h, n_vec, tail, shape.blocks_per_cu, kPairLg, g,
+                                                s);
       return launch_runs<Op, NS, NO, 1, NT>(h, n_vec, tail, shape.blocks_per_cu, kRunLg, g, s);
     }
   }
@@ -704,8 +651,6 @@ __device__ __forceinline__ void res_load(u32x4 (&v)[T][NS], const ResArgs<NS> &a
     }
 }
 
-constexpr uint32_t kResPairLg = 12;  // pairs of runs lie 4096 vectors (64 KiB) apart
-
 // Bound by HBM reads: NS x ncover loads of 1 KiB per run of 64 residual
 // vectors.  The W waves of a block take the covering segments in turn, U at
 // a time with all their loads ahead of the arithmetic, into fp64 partial
@@ -733,7 +678,7 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
   for (int32_t q = 1; q < a.n_part; ++q)
     if (blockIdx.x >= a.part[q].tile) p = q;
   const ResPart part = a.part[p];
-  const RunTile tile = run_tile<T>(blockIdx.x - part.tile, part.n_vec, kResPairLg);
+  const RunTile tile = run_tile<T>(blockIdx.x - part.tile, part.n_vec, kPairLg);
   uint32_t live[T], l[T];  // vectors of a run; a lane's own (idle lanes repeat the last)
   uint64_t j0[T];
 #pragma unroll
@@ -852,7 +797,7 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
   uint32_t singles = 0;
   int ncover = 0;
   for (int i = 0; i < j.n_iv; ++i) {
-    singles += run_tiles<1>(uint32_t(j.iv[i].n_vec), kResPairLg);
+    singles += run_tiles<1>(uint32_t(j.iv[i].n_vec), kPairLg);
     ncover = std::max(ncover, int(j.iv[i].ncover));
   }
   const ResShape shape = within_grid(
@@ -862,7 +807,7 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
   for (int i = 0, first = 0; i < j.n_iv; first += j.iv[i].ncover, ++i) {
     const uint32_t n_vec = uint32_t(j.iv[i].n_vec);
     a.part[i] = ResPart{tiles, uint32_t(j.iv[i].vec_begin), n_vec, first, j.iv[i].ncover};
-    tiles += shape.runs == 2 ? run_tiles<2>(n_vec, kResPairLg) : run_tiles<1>(n_vec, kResPairLg);
+    tiles += shape.runs == 2 ? run_tiles<2>(n_vec, kPairLg) : run_tiles<1>(n_vec, kPairLg);
   }
   auto launch = [&](auto waves, auto runs) {
     constexpr int W = decltype(waves)::value, T = decltype(runs)::value;

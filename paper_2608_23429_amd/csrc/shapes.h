@@ -1,11 +1,15 @@
-// How a launch is laid out: the residual kernel's blocks by its sizes, and the
-// LDS that limits how many blocks share a compute unit.  Host arithmetic.
+// How a launch is laid out: the prediction's and the residual kernel's blocks by
+// their sizes, and the LDS that limits how many share a compute unit.  Host
+// arithmetic.
 #pragma once
 
 #include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
+
+#include "cheb.h"
+#include "tiles.h"
 
 namespace cheb {
 
@@ -21,6 +25,70 @@ inline size_t lds_share(int lds_per_cu, int blocks) {
   const int per = lds_per_cu / blocks / 1280 * 1280;
   if (per <= kMost) return size_t(per);
   return lds_per_cu / kMost == blocks ? size_t(kMost) : 0;
+}
+
+// Runs per tile and how many one-wave blocks share a compute unit (0: no
+// limit) in a prediction, from the history size, the number of outputs, the
+// layout and the work.  Too few blocks leave the memory latency uncovered, too
+// many flood the memory queues and slow the writes.  Measured on MI355X, bf16,
+// entries of 30 MB to 1.6 GB, 2 to 8 of each kind:
+//  - one output: about 40 KiB of loads in flight from interleaved entries, 45
+//    to 48 from contiguous ones (6 interleaved entries of 1.6 GB: 1627 us with
+//    7, 1642 with 6, over 1670 with 8; 5 contiguous ones: 1417 us with 9, 1447
+//    with 10);
+//  - several outputs: about 60 KiB of loads and stores (2 interleaved entries,
+//    5 outputs: 9 blocks, 6% less time than 12), and not below 6 to 8 (8
+//    interleaved entries, 4 or 5 outputs: 7, 1% less than 6); one block less
+//    for two outputs of 6 or 8 interleaved entries (8: 2.5%);
+//  - a call of under 512 KiB a compute unit is over before the queues fill
+//    and wants twice as many (6 entries of 9 MB: 11.4 us with 16, 12.6 with
+//    7);
+//  - above that, contiguous entries in tiles of two runs 64 KiB apart, which
+//    share DRAM rows: one output of 3 to 5 entries (3 of 264 MB 159 us -> 154;
+//    5 of 528 MB 473 -> 467) and several outputs (2 entries, 5 outputs of 264
+//    MB: 289 us -> 282; 6 entries, 3 outputs of 1.06 GB in fp16: 1452 -> 1434;
+//    4 to 8 entries, 3 to 5 outputs: 1 to 3% where the entries' size is a
+//    multiple of some MiB, as models' are, and -1 to 1% where it is odd), with
+//    6 blocks where that is 45 KiB (4 to 6 entries, 3 outputs: 1% over 5).  Two
+//    outputs of 5 entries or more gain 1 to 2.5% without, one output of 6 or
+//    more 2%, one or two entries 1%; interleaved entries gain nothing by it.
+struct StreamShape {
+  int blocks_per_cu;  // 0: no limit
+  int runs = 1;
+};
+
+constexpr uint32_t kPairLg = 12;  // pairs of runs lie 4096 vectors (64 KiB) apart
+
+constexpr bool takes_pairs(int ns, int no) {
+  return no == 1 ? ns >= 3 && ns <= 5 : no == 2 ? ns <= 4 : true;
+}
+
+inline bool large_call(int ns, int no, uint32_t n_vec, int cus) {
+  return uint64_t(n_vec / kRun) * uint64_t(ns + no) >= 512u * uint64_t(cus);
+}
+
+// Blocks of single runs.
+inline int single_blocks(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
+  static constexpr int kOne[2][CHEB_MAX_SLOTS + 1] = {{0, 0, 0, 16, 11, 9, 8, 7, 6},
+                                                      {0, 0, 0, 14, 9, 8, 7, 6, 5}};
+  const int sum = ns + no;
+  int blocks = kOne[interleaved][ns];
+  if (no > 1) {
+    const int least = sum >= 12 && (ns < 8 || !interleaved) ? 6 : sum <= 9 && !interleaved ? 8 : 7;
+    blocks = std::max(least, (60 + sum / 2) / sum);
+    if (interleaved && no == 2 && (ns == 6 || ns == 8)) --blocks;
+  }
+  return large_call(ns, no, n_vec, cus) ? blocks : 2 * blocks;
+}
+
+inline StreamShape stream_shape(int ns, int no, bool interleaved, uint32_t n_vec, int cus) {
+  if (!interleaved && takes_pairs(ns, no) && large_call(ns, no, n_vec, cus)) {
+    const int sum = ns + no;
+    if (no == 1) return {(28 + sum / 2) / sum, 2};
+    if (sum == 7 || (no == 3 && sum > 7 && sum <= 9)) return {6, 2};
+    return {std::max(sum >= 14 ? 4 : 5, (36 + sum / 2) / sum), 2};
+  }
+  return {single_blocks(ns, no, interleaved, n_vec, cus)};
 }
 
 // Waves per block, how many of its blocks share a compute unit and runs per

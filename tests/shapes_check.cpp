@@ -1,4 +1,6 @@
-// The residual kernel's launch shapes, on the CPU: over every history size,
+// The kernels' launch shapes, on the CPU.  Predictions: pairs of runs only where
+// the library holds that kernel, and no pairs of interleaved entries, whose
+// chunks they would leave.  Residuals: over every history size,
 // storage type, layout and number of covering segments, and sizes up to the
 // last one a residual may have, the grid stays within HIP's 2^32 - 1 threads.
 // Reserved LDS lets as many blocks onto a compute unit as wanted and (to 12, where
@@ -41,8 +43,25 @@ static void check_lds() {
     }
 }
 
+static void check_stream(int ns, int no, uint32_t n_vec) {
+  for (int interleaved = 0; interleaved < 2; ++interleaved) {
+    const StreamShape s = stream_shape(ns, no, interleaved != 0, n_vec, 256);
+    const bool two = s.runs == 2 && !interleaved && takes_pairs(ns, no);
+    if ((s.runs != 1 && !two) || s.blocks_per_cu < 0 ||
+        (s.blocks_per_cu == 0 && (ns > 2 || no > 1))) {
+      fprintf(stderr, "%d entries, %d outputs, %u vectors: %d runs, %d blocks\n", ns, no, n_vec,
+              s.runs, s.blocks_per_cu);
+      exit(1);
+    }
+  }
+}
+
 int main() {
   check_lds();
+  for (int ns = 1; ns <= 8; ++ns)
+    for (int no = 1; no <= 8; ++no)
+      for (uint32_t n_vec : {0u, 1u, 1u << 15, 1u << 20, 1u << 25, (1u << 31) - 1})
+        check_stream(ns, no, n_vec);
   const uint32_t sizes[] = {1, 64, 65, 1u << 14, 1u << 20, 1u << 25, (1u << 28) - 64, 1u << 28,
                             1u << 29, (1u << 30) - 64, (1u << 30) - 1, 1u << 30,
                             (1u << 30) + 1, (1u << 31) - 65, (1u << 31) - 1};
