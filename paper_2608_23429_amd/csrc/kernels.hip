@@ -616,6 +616,7 @@ struct ResArgs {
   int64_t delta[kResCover];  // vectors, from an entry's base to the segment's residual vector 0
   ResPart part[kResIntervals];
   int32_t n_part;
+  uint32_t n_tiles;
   const float *x_in;  // may be null: zero
   float *x_out;
   uint64_t super;
@@ -652,33 +653,38 @@ __device__ __forceinline__ void res_load(u32x4 (&v)[T][NS], const ResArgs<NS> &a
 }
 
 // Bound by HBM reads: NS x ncover loads of 1 KiB per run of 64 residual
-// vectors.  The W waves of a block take the covering segments in turn, U at
-// a time with all their loads ahead of the arithmetic, into fp64 partial
-// sums of the same vectors, and add those up through LDS.  Dividing the
-// segments among waves gives a small residual W times the waves to fill the
-// chip with, and has the blocks in flight read neighbouring kilobytes of a
-// few places at a time rather than 16 KiB runs of every place.  Measured on
-// MI355X against one residual vector per lane of 1024-lane blocks: the
-// FLUX-1024 cache, 6 interleaved entries, 1566 -> 1447 us (6.3 -> 6.8 TB/s);
-// DiT-XL/2 256 for one image (56 segments, 1152 tiles), 3 entries, 66 -> 35
-// us; an eighth of it (144 tiles), 54 -> 10 us.
+// vectors.  Either the W waves of a block share a tile (G = 1): they take the
+// covering segments in turn, U at a time with all their loads ahead of the
+// arithmetic, into fp64 partial sums of the same vectors, and add those up
+// through LDS.  Dividing the segments among waves gives a small residual W
+// times the waves to fill the chip with, and has the blocks in flight read
+// neighbouring kilobytes of a few places at a time rather than 16 KiB runs of
+// every place.  Or each of a block's G waves has a tile of its own (W = 1),
+// which keeps neighbouring tiles together on a compute unit.  residual_shape
+// says which.  Measured on MI355X against one residual vector per lane of
+// 1024-lane blocks: the FLUX-1024 cache, 6 interleaved entries, 1566 -> 1447
+// us (6.3 -> 6.8 TB/s); DiT-XL/2 256 for one image (56 segments, 1152 tiles),
+// 3 entries, 66 -> 33 us; an eighth of it (144 tiles), 54 -> 10 us.
 // From contiguous memory a wave reads two runs 64 KiB apart (T = 2) at once:
 // kilobytes at that distance share open DRAM rows, which the many far places
 // a tile reads would otherwise close between them (FLUX-1024, 6 contiguous
 // entries, 1600 -> 1454 us; one entry, 292 -> 266; at 16 KiB apart 1.5 to 3%
 // less, at 128 KiB nothing).  Interleaved entries have that neighbourhood
 // already and lose 2% by it.
-template <class Dec, int NS, int W, int U, int T>
-__global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
+template <class Dec, int NS, int W, int G, int U, int T>
+__global__ __launch_bounds__(64 * W * G) void residual_kernel(ResArgs<NS> a) {
+  static_assert(W == 1 || G == 1, "waves share a tile or have one each");
   constexpr int V = Dec::kVec;
   constexpr uint32_t kThreads = 64u * W;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t own = G == 1 ? blockIdx.x : blockIdx.x * uint32_t(G) + wave;
+  if (G > 1 && own >= a.n_tiles) return;
   int32_t p = 0;
   for (int32_t q = 1; q < a.n_part; ++q)
-    if (blockIdx.x >= a.part[q].tile) p = q;
+    if (own >= a.part[q].tile) p = q;
   const ResPart part = a.part[p];
-  const RunTile tile = run_tile<T>(blockIdx.x - part.tile, part.n_vec, kPairLg);
+  const RunTile tile = run_tile<T>(own - part.tile, part.n_vec, kPairLg);
   uint32_t live[T], l[T];  // vectors of a run; a lane's own (idle lanes repeat the last)
   uint64_t j0[T];
 #pragma unroll
@@ -708,28 +714,30 @@ __global__ __launch_bounds__(64 * W) void residual_kernel(ResArgs<NS> a) {
         x1[h] = *(reinterpret_cast<const u32x4 *>(a.x_in + (j0[i] + l[i]) * V) + h % (V / 4));
     }
   }
-  int32_t c = int32_t(wave) * U;
-  for (; c + U <= nc; c += W * U) {
-    u32x4 v[U][T][NS];
+  auto take = [&](auto count, int32_t at) {
+    constexpr int N = decltype(count)::value;
+    u32x4 v[N][T][NS];
 #pragma unroll
-    for (int u = 0; u < U; ++u) res_load(v[u], a, uint64_t(delta[c + u]), j0, l);
+    for (int u = 0; u < N; ++u) res_load(v[u], a, uint64_t(delta[at + u]), j0, l);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < N; ++u)
 #pragma unroll
       for (int i = 0; i < T; ++i)
 #pragma unroll
         for (int k = 0; k < NS; ++k) Dec::add(acc[i], v[u][i][k], a.w[k]);
+  };
+  int32_t c = G == 1 ? int32_t(wave) * U : 0;
+  for (; c + U <= nc; c += W * U) take(std::integral_constant<int, U>(), c);
+  // the last group, if it is this wave's and partial
+  if constexpr (U > 2) {
+    if (c + 2 <= nc) {
+      take(std::integral_constant<int, 2>(), c);
+      c += 2;
+    }
   }
   if constexpr (U > 1) {
-    for (; c < nc; ++c) {  // the last group, if it is this wave's and partial
-      u32x4 v[T][NS];
-      res_load(v, a, uint64_t(delta[c]), j0, l);
-#pragma unroll
-      for (int i = 0; i < T; ++i)
-#pragma unroll
-        for (int k = 0; k < NS; ++k) Dec::add(acc[i], v[i][k], a.w[k]);
-    }
+    for (; c < nc; ++c) take(std::integral_constant<int, 1>(), c);
   }
   if constexpr (W == 1) {
 #pragma unroll
@@ -809,29 +817,34 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
     a.part[i] = ResPart{tiles, uint32_t(j.iv[i].vec_begin), n_vec, first, j.iv[i].ncover};
     tiles += shape.runs == 2 ? run_tiles<2>(n_vec, kPairLg) : run_tiles<1>(n_vec, kPairLg);
   }
-  auto launch = [&](auto waves, auto runs) {
-    constexpr int W = decltype(waves)::value, T = decltype(runs)::value;
+  a.n_tiles = tiles;
+  auto launch = [&](auto waves, auto grouped, auto runs) {
+    constexpr int W = decltype(waves)::value, G = decltype(grouped)::value;
+    constexpr int T = decltype(runs)::value;
     // Segments a wave loads before its arithmetic.
-    constexpr int U = NS == 1 ? 4 / T : NS == 2 ? (T == 2 && W == 1 ? 1 : 2) : 1;
+    constexpr int U = G > 1       ? 2 / T
+                      : NS == 1   ? 4 / T
+                      : NS == 2   ? (T == 2 && W == 1 ? 1 : 2)
+                                  : 1;
     constexpr size_t kOwn = W > 1 ? size_t(W) * T * kRun * Dec::kVec * sizeof(double) : 0;
     const size_t extra = residual_lds(g.lds_per_cu, shape.blocks_per_cu, kOwn, g.waves);
-    hipLaunchKernelGGL((residual_kernel<Dec, NS, W, U, T>), dim3(tiles), dim3(64 * W), extra, s, a);
+    hipLaunchKernelGGL((residual_kernel<Dec, NS, W, G, U, T>), dim3((tiles + G - 1) / G),
+                       dim3(64 * W * G), extra, s, a);
   };
   const std::integral_constant<int, 1> one;
   const std::integral_constant<int, 2> two;
   const std::integral_constant<int, 4> four;
-  switch (shape.runs * 100 + shape.waves) {
-    case 101: launch(one, one); break;
-    case 102: launch(two, one); break;
-    case 104: launch(four, one); break;
-    case 201: launch(one, two); break;
-    case 202: launch(two, two); break;
-    case 204: launch(four, two); break;
-    case 116: launch(std::integral_constant<int, 16>(), one); break;
-    default:  // 8 waves
-      if constexpr (NS >= 7) launch(std::integral_constant<int, 8>(), one);
-      break;
-  }
+  const std::integral_constant<int, 16> sixteen;
+  if (shape.tiles == 16)
+    shape.runs == 2 ? launch(one, sixteen, two) : launch(one, sixteen, one);
+  else if (shape.waves == 16)
+    launch(sixteen, one, one);
+  else if (shape.waves == 4)
+    shape.runs == 2 ? launch(four, one, two) : launch(four, one, one);
+  else if (shape.waves == 2)
+    shape.runs == 2 ? launch(two, one, two) : launch(two, one, one);
+  else
+    shape.runs == 2 ? launch(one, one, two) : launch(one, one, one);
   return hipGetLastError();
 }
 

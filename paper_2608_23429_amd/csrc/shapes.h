@@ -91,58 +91,117 @@ inline StreamShape stream_shape(int ns, int no, bool interleaved, uint32_t n_vec
   return {single_blocks(ns, no, interleaved, n_vec, cus)};
 }
 
-// Waves per block, how many of its blocks share a compute unit and runs per
-// tile, from the sizes (measured on MI355X, 256 compute units, bf16 unless
-// said; cu = tiles of one run per compute unit):
-//  - one segment (a collapsed history) is a stream of ns reads plus the
-//    residual's own read and write: one wave, about 80 KiB of those a compute
-//    unit (fp32, 225K tiles: 6 entries 395 us with 10 blocks, 413 without a
-//    limit; 8 entries 470 with 8, 495);
-//  - up to 4 segments: little to divide.  One wave, which needs no LDS sum (4
-//    segments, 4.6K tiles, 3 entries: 14 us against 16 with 4 waves); two
-//    where the residual is large (3 segments, 52K tiles, 2 entries: 89 us
-//    against 91; but 2 segments in fp32, whose tiles are half as large, 42
-//    against 38);
-//  - below that: 16 waves under one tile a compute unit (144 tiles of 56
-//    segments, 3 entries: 10 us against 16 with 4), 4 under 4, 2 under 8 (1152
-//    tiles, 3 entries: 31.9 us against 33.2 with 4);
-//  - then contiguous entries take pairs of runs: one wave without a limit
-//    under cu = 32, the first third of it with single runs (2304 tiles, 3
-//    entries: 61 us against 65 with 4 waves; 6072 tiles of 24 segments, 6
-//    entries: 140 against 147), and 4 waves with few blocks beyond (9072
-//    tiles of 57 segments, 3 entries: 251 us with 2 blocks, 262 with 4 of
-//    single runs; 15 segments, 2 entries: 84 with 4, 99 with 2), but 2 waves
-//    for one entry and few segments (8 segments, 18K tiles: 35 us against 43);
-//  - interleaved entries 4 waves (8 for 7 entries or more), their blocks
-//    limited where there are many tiles (FLUX-1024, 57 segments, 27K tiles, 6
-//    entries: 1446 us with 2 blocks, 1463 with 3, 1497 without a limit; 15
-//    segments, 15K tiles, 8 entries: 281 with 2, 287 with 4).
+// The residual kernel's launch: the waves that share a tile, how many blocks
+// share a compute unit, runs per tile, and tiles per block where each wave has
+// one of its own.
 struct ResShape {
   int waves;
   int blocks_per_cu;  // 0: no limit
   int runs = 1;
+  int tiles = 1;
 };
 
+// By the sizes; cu stands for tiles of one run per compute unit.  The lines come
+// from sweeps on MI355X (256 compute units) of 1 to 8 entries in bf16, both
+// layouts, 1 to 57 segments and cu 0.5 to 150, of odd sizes and of models' own
+// (whole multiples of 64 KiB), against the 1024-lane kernel without division
+// ("lanes") as well; a line is drawn where both kinds of size gain by it.  In
+// microseconds:
+//  - one segment (a collapsed history) is a stream of ns reads plus the
+//    residual's own read and write: one wave, about 80 KiB of those a compute
+//    unit (fp32, 225K tiles: 6 entries 395 with 10 blocks, 413 without a limit;
+//    8 entries 470 with 8, 495);
+//  - up to 4 segments: little to divide, one wave, which needs no LDS sum (4
+//    segments, 4.6K tiles, 3 entries: 14 against 16 with 4 waves), except 4 waves
+//    for 5 interleaved entries or more (5 of 3 segments, cu 13.5: 13.1 against
+//    13.5) and 2 or 4 where the residual is large (3 segments, 52K tiles, 2
+//    entries: 89 against 91; 8 contiguous entries of 3, cu 27: 32.7 against
+//    33.6; but 2 segments in fp32, whose tiles are half as large, 42 against 38);
+//  - others, up to cu 4: 16 waves under one tile a compute unit (144 tiles of 56
+//    segments, 3 entries: 10 against 16 with 4), else 4;
+//  - to cu 8: 2 (1152 tiles of 56 segments, 3 entries: 31.9 against 33.2 with
+//    4), but one for 7 or 8 contiguous entries, which have loads enough (8 of 56,
+//    cu 5.2: 104 against 115), and 4 with few blocks for interleaved ones (8 of
+//    56, cu 5.2: 103 against 110);
+//  - about cu 10 to 16, where 16 waves a compute unit hold all tiles at once:
+//    blocks of 16 tiles, one wave each, whose neighbours then stay together (8
+//    contiguous entries of 8 segments, cu 13.5: 38.0, 39.2 in pairs of runs, 38.4
+//    lanes; 3 interleaved of 24, cu 13.5: 42.4, 44.4 divided among 4, 42.5
+//    lanes).  Past 16 a second round would run nearly empty (1.3 times the
+//    time).  Not so 5 segments (8 contiguous entries, cu 13.5: 29.5, 26.7 in
+//    pairs), and contiguous entries of over 12 gain nothing by it at models'
+//    sizes: pairs of runs, one wave;
+//  - contiguous entries to cu 24 in pairs of runs, one wave (2304 tiles of 56, 3
+//    entries: 61 against 65 with 4 waves), and to 32, where 16 waves hold all
+//    pairs, in blocks of 16 (3 of 24 segments, cu 27: 82.8, 86.6 in single blocks,
+//    89.2 lanes; 3 of 40, cu 28.7: 151, 161.5, 160);
+//  - contiguous ones beyond: up to 6 segments, and to 9 for up to 4 entries, 2
+//    waves, as 5 divided among 4 leave three idle for half of the time (5 entries
+//    of 5 segments, cu 43: 58.8, 69.5 with 4, 58.0 lanes); one entry of up to 31
+//    single runs (24 segments, cu 54: 61.6 against 64.0 in pairs); the others 4
+//    waves in pairs, few blocks (9072 tiles of 57 segments, 3 entries: 251 with
+//    2, 262 with 4 of single runs; 15 segments, 2 entries: 84 with 4, 99 with 2;
+//    FLUX-1024's reduction, one entry of 57 segments: 270 with 3, 283 with one
+//    wave);
+//  - interleaved ones: one or 2 waves for 2 entries of up to 12 segments (8, cu
+//    27: 24.8 against 26.4 with 4), else 4, their blocks limited by the loads in
+//    flight (FLUX-1024, 57 segments, 27K tiles, 6 entries: 1446 with 2 blocks,
+//    1463 with 3, 1497 without a limit; 7 entries of 5, cu 42: 72.8 with 3, 80.5
+//    with 2 of 8 waves).
 inline ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, bool contiguous,
                                int cus) {
-  const uint32_t per_cu = tiles / uint32_t(cus);
-  if (ncover == 1 && per_cu >= 32) return {1, 80 / (ns + vec / 2)};
-  if (ncover <= 1 || (ncover <= 4 && per_cu < 64)) return {1, 0};
-  if (ncover == 2 && vec == 4) return {1, 0};
-  if (ncover <= 4 && contiguous) return {2, ns >= 5 ? 4 : 0, 2};
-  if (ncover <= 4) return {2, ns >= 7 ? 4 : ns >= 3 ? 8 : 0};
-  if (per_cu < 1 && ncover >= 16) return {16, 0};
-  if (per_cu < 4) return {4, 0};
-  if (per_cu < 8) return {2, 0};
+  const auto upto = [&](int n) { return tiles <= uint64_t(n) * uint64_t(cus); };
+  const bool few = ncover <= 4;
+  if (ncover == 1 && tiles >= 32u * uint32_t(cus)) return {1, 80 / (ns + vec / 2)};
+  if (ncover <= 1) return {1, 0};
+  if (upto(4) && !few) return {ncover >= 16 && tiles < uint32_t(cus) ? 16 : 4, 0};
+  if (upto(16) && few) {
+    if (ncover == 2 || upto(4)) return {1, 0};
+    if (!contiguous) return {ns >= 5 && !upto(6) ? 4 : 1, 0};
+    if (upto(12) || ns == 3 || ns == 4) return {1, 0};
+    return ns <= 2 ? ResShape{1, 0, 2} : ResShape{1, 0, 1, 16};
+  }
   if (contiguous) {
-    if (per_cu < 32) return {1, 0, per_cu < 12 ? 1 : 2};
-    if (ns == 1) return ncover >= 24 ? ResShape{4, 3, 2} : ResShape{2, 0, 2};
+    if (few) {
+      if (upto(32) && ns >= 7 && ncover > 2 && !upto(24)) return {4, 0};
+      if (upto(64) && (ns <= 2 || ncover == 2 || upto(32))) return {1, 0};
+      if (ncover == 2 && vec == 4) return {1, 0};
+      if (upto(64)) return {2, 8};
+      return {2, ns >= 5 ? 4 : 0, 2};
+    }
+    if (upto(8)) return {ns >= 7 ? 1 : 2, 0};
+    if (upto(12)) return {1, 0};
+    if (upto(16)) return ncover >= 7 && ncover <= 12 && ns >= 3 ? ResShape{1, 0, 1, 16}
+                                                                : ResShape{1, 0, 2};
+    if (upto(24)) return {1, 0, 2};
+    if (ns == 1 && ncover <= 9) return {upto(32) ? 1 : 2, 0};
+    if (upto(32)) return {1, 0, 2, 16};
+    if (ns == 1 && ncover < 24) return {2, 0, 2};
+    if (ns == 1) return ncover < 32 ? ResShape{4, 8} : ResShape{4, 3, 2};
+    if (ncover <= 6 || (ncover <= 9 && ns <= 4)) return {2, 8};
+    if (ncover <= 9) return {4, ns <= 6 || upto(64) ? 3 : 2, 2};
     if (ns >= 5) return {4, 2, 2};
     return {4, ncover < 32 ? 4 : ns == 2 ? 3 : 2, 2};
   }
-  if (per_cu < 16) return {4, 0};
-  if (ns >= 7) return {8, 2};
-  return {4, ncover >= 24 ? std::max(2, 4 - ns / 2) : 4};
+  if (few) {
+    if (ncover == 2 ? upto(64) : upto(ns >= 7 ? 24 : 32) || (upto(64) && ns == 2)) return {1, 0};
+    if (upto(64)) return {4, ns >= 7 ? 4 : 8};
+    if (ncover == 2 && vec == 4) return {1, 0};
+    return {2, ns >= 7 ? 4 : ns >= 3 ? 8 : 0};
+  }
+  if (upto(8)) return ns >= 7 ? ResShape{4, ncover <= 6 ? 0 : 3} : ResShape{2, 0};
+  if (upto(16)) {
+    if (ns >= 7) return {4, ncover < 16 ? 0 : upto(10) ? 3 : 2};
+    if (upto(10)) return {ns * ncover >= 120 ? 1 : 4, 0};
+    return (ns <= 4 && ncover >= 7) || ncover >= 40 ? ResShape{1, 0, 1, 16} : ResShape{4, 0};
+  }
+  if (ncover <= 12) {
+    if (ns == 2) return upto(32) ? ResShape{1, 0} : ResShape{2, 8};
+    if (ns <= 4) return {4, ncover <= 6 || upto(48) ? 8 : 4};
+    return {4, ns <= 6 || ncover <= 6 ? 4 : upto(64) ? 3 : 2};
+  }
+  if (ns <= 4 && ncover < 40 && upto(32)) return {4, ns == 2 ? 8 : 4};
+  return {4, ns >= 7 || ncover >= 24 ? std::max(2, 4 - ns / 2) : 4};
 }
 
 // LDS reserved on top of a block's own so that `blocks` of them share a compute
@@ -159,7 +218,7 @@ inline size_t residual_lds(int lds_per_cu, int blocks, size_t own, int waves_per
 // tile and as many waves a compute unit.
 inline ResShape within_grid(ResShape s, uint32_t tiles) {
   if (uint64_t(tiles) * uint64_t(64 * s.waves) <= UINT32_MAX) return s;
-  return {1, s.blocks_per_cu * s.waves, s.runs};
+  return {1, s.blocks_per_cu * s.waves, s.runs, s.tiles};
 }
 
 }  // namespace cheb

@@ -19,8 +19,14 @@ static void check_grid(int ns, int vec, int ncover, uint32_t n_vec, bool contigu
   const ResShape s =
       within_grid(residual_shape(ns, vec, ncover, singles, contiguous, 256), singles);
   const uint64_t tiles = s.runs == 2 ? run_tiles<2>(n_vec, 12) : singles;
-  const uint64_t threads = tiles * 64u * uint64_t(s.waves);
-  if (s.waves < 1 || s.blocks_per_cu < 0 || threads == 0 || threads > UINT32_MAX) {
+  const uint64_t per_block = uint64_t(s.waves) * uint64_t(s.tiles);
+  const uint64_t threads = (tiles + s.tiles - 1) / s.tiles * 64u * per_block;
+  // The kernels that are held: waves share a tile or have one each.
+  const bool held = s.tiles == 1 ? s.waves == 1 || s.waves == 2 || s.waves == 4 ||
+                                       (s.waves == 16 && s.runs == 1)
+                                 : s.waves == 1 && s.tiles == 16;
+  const bool runs = s.runs == 1 || (s.runs == 2 && contiguous);
+  if (!held || !runs || s.blocks_per_cu < 0 || threads == 0 || threads > UINT32_MAX) {
     fprintf(stderr, "%d entries, %d segments, %u vectors of %d: %d waves, %llu threads\n", ns,
             ncover, n_vec, vec, s.waves, (unsigned long long)threads);
     exit(1);
@@ -62,7 +68,9 @@ int main() {
     for (int no = 1; no <= 8; ++no)
       for (uint32_t n_vec : {0u, 1u, 1u << 15, 1u << 20, 1u << 25, (1u << 31) - 1})
         check_stream(ns, no, n_vec);
-  const uint32_t sizes[] = {1, 64, 65, 1u << 14, 1u << 20, 1u << 25, (1u << 28) - 64, 1u << 28,
+  const uint32_t sizes[] = {1, 64, 65, 1u << 14, 5u << 14, 9u << 14, 13u << 14, 17u << 14,
+                            20u << 14, 28u << 14, 40u << 14, 1u << 20, 80u << 14, 1u << 25,
+                            (1u << 28) - 64, 1u << 28,
                             1u << 29, (1u << 30) - 64, (1u << 30) - 1, 1u << 30,
                             (1u << 30) + 1, (1u << 31) - 65, (1u << 31) - 1};
   for (int ns = 1; ns <= 8; ++ns)

@@ -1,6 +1,7 @@
-"""The residual kernel's launch shapes: tiles of 64 vectors shared by 1, 2, 4,
-8 or 16 waves, several residual intervals in one launch, and tiles that cross
-the chunks of an interleaved entry, against the oracle."""
+"""The residual kernel's launch shapes: tiles of 64 vectors shared by 1, 2, 4 or
+16 waves, blocks of 16 tiles with a wave each, several residual intervals in
+one launch, and tiles that cross the chunks of an interleaved entry, against
+the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -66,6 +67,23 @@ def test_many_tiles(layout, n, ncover, vecs):
     """Residuals past each size at which the rule changes; odd vector counts
     put later segments' tiles across chunk ends."""
     _check("bf16", n, [vecs * 8] * ncover, [0] * ncover, vecs * 8, layout, True, ncover)
+
+
+@pytest.mark.parametrize("layout", ["slots", "interleaved"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,ncover,tiles", [(4, 5, 13), (3, 3, 13), (8, 7, 14), (2, 9, 15),
+                                            (1, 3, 5), (1, 2, 40), (1, 13, 28), (3, 5, 28),
+                                            (5, 6, 40), (8, 3, 33)])
+def test_blocks_of_tiles(layout, dtype, n, ncover, tiles):
+    """Blocks of 16 tiles (single runs and pairs), the last block partly idle
+    and the last tile partly filled; two intervals, so that a block holds tiles
+    of both; numbers of segments that the loads of 2 or 4 do not divide."""
+    vec = 4 if dtype == "f32" else 8
+    vecs = tiles * 64 * 256 - 64 * 5 - 31
+    head = 64 * 37 + 5                          # the first segments cover only this
+    _check(dtype, n, [vecs * vec] * ncover, [0] * ncover, vecs * vec, layout, ncover % 2 == 1, n)
+    _check(dtype, n, [head * vec] * 2 + [vecs * vec] * (ncover - 1), [0] * (ncover + 1),
+           vecs * vec, layout, ncover % 2 == 0, n)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
