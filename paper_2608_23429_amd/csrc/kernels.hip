@@ -347,21 +347,6 @@ int auto_waves(int ns, int no) {
   return std::max(6, (kib + ns / 2) / ns);
 }
 
-// The same for the other launch shapes, so that about `waves` waves of the
-// kernel share a compute unit (the LDS is what runs out): an equal share of
-// the compute unit's LDS, rounded down to 512 bytes.  Zero when there is no
-// cap, when the cap is at the hardware's own limit, or when one block would
-// need more than the default 64 KiB of dynamic LDS.
-template <int BLK>
-size_t occupancy_lds(const Gpu &g) {
-  constexpr int kWavesPerBlock = BLK / 64;
-  if (g.waves <= 0 || g.lds_per_cu <= 0) return 0;
-  const int blocks = std::max(1, g.waves / kWavesPerBlock);
-  if (blocks * kWavesPerBlock >= 32) return 0;
-  const size_t per = size_t(g.lds_per_cu / blocks) / 512 * 512;
-  return per <= size_t(64) << 10 ? per : 0;
-}
-
 template <class Op, int NS, int NO, int BLK, int U, bool NT>
 hipError_t launch_shape(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, Tail tail,
                         int blocks_per_cu, const Gpu &g, hipStream_t s) {
@@ -370,7 +355,7 @@ hipError_t launch_shape(const Hist<NS, NO, typename Op::W> &h, uint32_t n_vec, T
   uint32_t grid = std::max<uint32_t>(n_tiles, 1u);
   if (blocks_per_cu > 0) grid = std::min<uint32_t>(grid, uint32_t(blocks_per_cu) * uint32_t(g.cus));
   hipLaunchKernelGGL((combine_kernel<Op, NS, NO, BLK, U, NT>), dim3(grid), dim3(BLK),
-                     occupancy_lds<BLK>(g), s, h, n_vec, n_tiles, tail);
+                     occupancy_lds(g.lds_per_cu, g.waves, BLK / 64), s, h, n_vec, n_tiles, tail);
   return hipGetLastError();
 }
 

@@ -13,18 +13,31 @@
 
 namespace cheb {
 
+// LDS is handed out in units of 1280 bytes on gfx950, and a block may have 64 KiB
+// of it.
+constexpr int kLdsUnit = 1280, kMostLds = 64 << 10;
+
 // Dynamic LDS a block reserves, and never touches, when `blocks` of them are
-// to share a compute unit: an equal share rounded down to the 1280-byte unit
-// LDS is handed out in on gfx950 (a size in between takes the next unit, and
-// one block fewer fits).  A share past the 64 KiB a block may have is cut to
-// that, if as many blocks still fit and no more.  Zero when there is no limit
-// or none is possible.
+// to share a compute unit: an equal share rounded down to the unit (a size in
+// between takes the next one, and one block fewer fits).  A share past what a
+// block may have is cut to that, if as many blocks still fit and no more.
+// Zero when there is no limit or none is possible.
 inline size_t lds_share(int lds_per_cu, int blocks) {
-  constexpr int kMost = 64 << 10;
   if (blocks <= 0 || lds_per_cu <= 0) return 0;
-  const int per = lds_per_cu / blocks / 1280 * 1280;
-  if (per <= kMost) return size_t(per);
-  return lds_per_cu / kMost == blocks ? size_t(kMost) : 0;
+  const int per = lds_per_cu / blocks / kLdsUnit * kLdsUnit;
+  if (per <= kMostLds) return size_t(per);
+  return lds_per_cu / kMostLds == blocks ? size_t(kMostLds) : 0;
+}
+
+// The same for the prediction's other launch shapes, so that as many blocks as
+// hold `waves` waves share a compute unit.  Zero when there is no cap, when the
+// cap is at the hardware's own limit, or when one block would need more than
+// the default 64 KiB of dynamic LDS.
+inline size_t occupancy_lds(int lds_per_cu, int waves, int waves_per_block) {
+  const int blocks = std::max(1, waves / waves_per_block);
+  if (waves <= 0 || lds_per_cu <= 0 || blocks * waves_per_block >= 32) return 0;
+  const int per = lds_per_cu / blocks / kLdsUnit * kLdsUnit;
+  return per <= kMostLds ? size_t(per) : 0;
 }
 
 // Runs per tile and how many one-wave blocks share a compute unit (0: no

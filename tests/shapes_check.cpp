@@ -34,7 +34,21 @@ static void check_grid(int ns, int vec, int ncover, uint32_t n_vec, bool contigu
 }
 
 static void check_lds() {
-  constexpr int kCu = 160 << 10, kUnit = 1280;   // handed out in whole units
+  constexpr int kCu = 160 << 10, kUnit = kLdsUnit;
+  // The tuning interface's cap: as many blocks as hold that many waves.
+  for (int per_block : {1, 4})
+    for (int waves = -1; waves <= 32; ++waves) {
+      const int blocks = waves < per_block ? 1 : waves / per_block;
+      const size_t lds = occupancy_lds(kCu, waves, per_block);
+      const size_t taken = (lds + kUnit - 1) / kUnit * kUnit;
+      const bool capped = waves > 0 && blocks >= 3 && blocks * per_block < 32;
+      if ((lds != 0) != capped ||
+          (capped && (taken * blocks > size_t(kCu) ||
+                      (blocks <= 12 && taken * (blocks + 1) <= size_t(kCu))))) {
+        fprintf(stderr, "%d waves in blocks of %d: %zu reserved\n", waves, per_block, lds);
+        exit(1);
+      }
+    }
   for (int blocks = 0; blocks <= 32; ++blocks)
     for (size_t own = 0; own <= 64u << 10; own += 512) {
       const size_t extra = residual_lds(kCu, blocks, own, 0), all = own + extra;
