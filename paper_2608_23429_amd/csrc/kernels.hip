@@ -820,9 +820,12 @@ hipError_t launch_residual_ns(const ResJob &j, const Gpu &g, hipStream_t s) {
   const std::integral_constant<int, 2> two;
   const std::integral_constant<int, 4> four;
   const std::integral_constant<int, 16> sixteen;
-  if (shape.tiles == 16)
-    shape.runs == 2 ? launch(one, sixteen, two) : launch(one, sixteen, one);
-  else if (shape.waves == 16)
+  if (shape.tiles == 16) {
+    if constexpr (NS == 1)  // contiguous, and never in blocks of single runs
+      launch(one, sixteen, two);
+    else
+      shape.runs == 2 ? launch(one, sixteen, two) : launch(one, sixteen, one);
+  } else if (shape.waves == 16)
     launch(sixteen, one, one);
   else if (shape.waves == 4)
     shape.runs == 2 ? launch(four, one, two) : launch(four, one, one);

@@ -24,7 +24,7 @@ static void check_grid(int ns, int vec, int ncover, uint32_t n_vec, bool contigu
   // The kernels that are held: waves share a tile or have one each.
   const bool held = s.tiles == 1 ? s.waves == 1 || s.waves == 2 || s.waves == 4 ||
                                        (s.waves == 16 && s.runs == 1)
-                                 : s.waves == 1 && s.tiles == 16;
+                                 : s.waves == 1 && s.tiles == 16 && (ns > 1 || s.runs == 2);
   const bool runs = s.runs == 1 || (s.runs == 2 && contiguous);
   if (!held || !runs || s.blocks_per_cu < 0 || threads == 0 || threads > UINT32_MAX) {
     fprintf(stderr, "%d entries, %d segments, %u vectors of %d: %d waves, %llu threads\n", ns,
@@ -91,7 +91,7 @@ int main() {
     for (int vec = 4; vec <= 8; vec += 4)
       for (int ncover = 0; ncover <= 128; ++ncover)
         for (uint32_t n_vec : sizes)
-          for (int contiguous = 0; contiguous < 2; ++contiguous)
+          for (int contiguous = ns == 1; contiguous < 2; ++contiguous)
             check_grid(ns, vec, ncover, n_vec, contiguous != 0);
   printf("shapes ok\n");
   return 0;
