@@ -537,7 +537,8 @@ CHEB_API int cheb_residual_reduce(const void *const *seg_src, const int64_t *seg
  *                cap for n <= 2 and one output; twice as many for a call of
  *                under 512 KiB a compute unit; about half where a wave takes
  *                two vectors per lane, in large calls over contiguous entries
- *                with several outputs or 3 to 5 entries), for the others
+ *                with several outputs, two of up to 4 entries only, or with 3
+ *                to 5 entries and one), for the others
  *                max(6, 44/n rounded) for one output and max(6, 36/n rounded)
  *                for several, no cap for n <= 2; -1: no cap; 1..32: that cap.
  *                Each block reserves an equal share of the compute unit's

@@ -1,6 +1,7 @@
 """The push's 64-vector tiles: segments around a tile's end, ragged and empty
 ones, very unlike sizes (several launches, largest first), equal ones that
-start anywhere in a tile, and more segments than one launch takes, read back bit for bit with zeroed padding."""
+start anywhere in a tile, and more segments than one launch takes, read back
+bit for bit with zeroed padding."""
 import pytest
 import torch
 
