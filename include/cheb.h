@@ -292,7 +292,8 @@ CHEB_API int cheb_cache_reset(cheb_cache *c);
  * oldest entry (or the next free one), zero-fills the padding after each
  * segment, records t and advances the ring (Algorithm 1, full computation:
  * store (s, f_s) in H; Section 3.3, the oldest entry is evicted).  One
- * launch per 64 segments of like size, asynchronous on `stream`.
+ * launch per 64 segments, or more where sizes differ widely, asynchronous on
+ * `stream`.
  * A launch failure (CHEB_E_HIP) after the arguments were accepted leaves
  * the history without the entry whose slot the copy was writing: a full
  * ring has dropped its oldest entry (the launches before the failing one

@@ -171,28 +171,59 @@ int order_segments(GatherSeg *segs, int n) {
   return held;
 }
 
-// Segments go in launches of up to 64 whose sizes are alike: a launch's grid
-// is as wide as its largest segment, and every block past the end of a
-// smaller one still costs its dispatch (about 4.7 blocks a nanosecond on
-// MI355X).  A launch is closed before the blocks without work would pass
-// 16384, about what another launch costs (FLUX-1024: three launches with 15K
-// idle blocks of 1.6M in place of two with 525K of 2.1M).
-int next_gather(const GatherSeg *segs, int n, int64_t vec, uint32_t *tiles) {
-  constexpr int64_t kIdleBlocks = 16384;
-  int64_t most = 0, idle = 0;
-  int used = 0;
-  for (; used < n && used < kGatherSegs; ++used) {
-    const int64_t vecs = (segs[used].numel + vec - 1) / vec;
-    const int64_t first = segs[used].dst_offset / vec;
-    const int64_t own = (first % kGatherTileVecs + vecs + kGatherTileVecs - 1) / kGatherTileVecs;
-    const int64_t wide = std::max(most, own);
-    const int64_t more = used * (wide - most) + (wide - own);
-    if (idle + more > kIdleBlocks) break;
-    most = wide;
-    idle += more;
+// A block past the end of its segment still costs its dispatch (about 4.7 blocks
+// a nanosecond on MI355X), another launch 4 to 5 us, and finding its class 2 to 5%
+// of a small step (76 tensors of three sizes, 25 MB: 13.9 us in classes, 13.2 flat
+// with 8K idle blocks; 64 tensors, 64 MB: 23.3 in classes, 27.2 in two flat
+// launches).  So a launch is flat while it has up to 10240 blocks without work,
+// as a DiT step always has, and else in classes, each as wide as its largest
+// segment with segments down to 7/8 of that (a FLUX-1024 step has two).  When the
+// classes run out, the last one goes on until 24576 of its blocks were idle.
+// From 2^20 blocks on the first class goes alone and flat, as another launch is
+// nothing then (FLUX-1024: 484.6 us as 57 and 19 tensors, 488.3 as 64 in classes
+// and 12).
+GatherPlan next_gather(const GatherSeg *segs, int n, int64_t vec, int64_t super_vecs) {
+  constexpr int64_t kIdleBlocks = 24576;
+  GatherPlan p;
+  p.segs = p.classes = 0;
+  int64_t blocks = 0, idle = 0, widest = 0, tiles = 0;
+  // Tiles are whole in an interleaved entry, so that none crosses a chunk, and
+  // in any entry where a segment starts inside 64 bytes, which two blocks would
+  // write in parts (18 bf16 tensors of 71 MB: 400 us, 425 cut from their starts).
+  p.whole = super_vecs != kChunkVecs;
+  for (int j = 0; j < n && j < kGatherSegs; ++j)
+    p.whole = p.whole || segs[j].dst_offset / vec % 4 != 0;
+  while (p.segs < n && p.segs < kGatherSegs) {
+    const int64_t vecs = (segs[p.segs].numel + vec - 1) / vec;
+    const int64_t lead = gather_lead(segs[p.segs].dst_offset / vec, p.whole);
+    const int64_t own = (lead + vecs + kGatherTileVecs - 1) / kGatherTileVecs;
+    GatherClass *c = p.classes ? &p.cls[p.classes - 1] : nullptr;
+    // A segment of the first one's size may have a tile more by its lead.
+    if (!c || own > c->tiles || (own < int64_t(c->tiles) * 7 / 8 && p.classes < kGatherClasses)) {
+      if (p.classes == kGatherClasses) break;
+      c = &p.cls[p.classes++];
+      *c = GatherClass{uint32_t(blocks), uint32_t(own), 0, p.segs};
+      c->inverse = own == 1 ? UINT32_MAX : uint32_t((uint64_t(1) << 32) / uint64_t(own));
+      idle = 0;
+    }
+    if (idle + c->tiles - own > kIdleBlocks && p.classes == kGatherClasses) break;
+    idle += c->tiles - own;
+    blocks += c->tiles;
+    tiles += own;
+    widest = std::max(widest, own);
+    ++p.segs;
   }
-  *tiles = uint32_t(most);
-  return used;
+  p.blocks = uint32_t(blocks);
+  p.widest = uint32_t(widest);
+  p.flat = widest * p.segs - tiles <= 10240;
+  if (!p.flat && blocks >= int64_t(1) << 20) {
+    p.segs = p.cls[1].seg;
+    p.classes = 1;
+    p.blocks = p.cls[1].block;
+    p.widest = p.cls[0].tiles;
+    p.flat = true;
+  }
+  return p;
 }
 
 }  // namespace cheb

@@ -82,13 +82,30 @@ int launch_gather(int dtype, void *slot_base, GatherSeg *segs, int n_segs, int64
 
 // The launches of a segment copy (cache.cpp).  order_segments() puts the
 // segments that are not empty in front, larger ones first, and returns their
-// number; next_gather() says how many of the first of them the next launch
-// takes (at least one) and how many tiles of kGatherTileVecs 16-byte vectors
-// its largest has.
-constexpr int kGatherSegs = 64;
+// number; next_gather() plans the next launch: how many of the first of them
+// it takes (at least one), as a grid of `widest` tiles of kGatherTileVecs 16-byte
+// vectors for each segment (flat), or as classes of like size in a row of
+// blocks: block b of a class copies tile (b - block) % tiles of segment seg +
+// (b - block) / tiles; `inverse` is 2^32 / tiles, rounded down.
+constexpr int kGatherSegs = 64, kGatherClasses = 16;
 constexpr int64_t kGatherTileVecs = 64;
+struct GatherClass {
+  uint32_t block, tiles, inverse;
+  int32_t seg;
+};
+struct GatherPlan {
+  int segs, classes;
+  uint32_t blocks, widest;
+  bool flat, whole;  // whole: tiles whole in the entry, not in the segment
+  GatherClass cls[kGatherClasses];
+};
 int order_segments(GatherSeg *segs, int n);
-int next_gather(const GatherSeg *segs, int n, int64_t vec, uint32_t *tiles);
+GatherPlan next_gather(const GatherSeg *segs, int n, int64_t vec, int64_t super_vecs);
+
+// Idle vectors at the start of a segment's first tile.
+inline int64_t gather_lead(int64_t dst_vec, bool whole) {
+  return whole ? dst_vec % kGatherTileVecs : 0;
+}
 
 // Read-only view of a cache's layout and ring state (cache.cpp).
 struct CacheView {

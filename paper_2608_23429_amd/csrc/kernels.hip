@@ -14,7 +14,7 @@
 //    (v_cvt_pk_bf16_f32, v_cvt_pk_f16_f32).  No LDS: nothing is reused
 //    across lanes.
 // 2. The full-step push (Algorithm 1, full computation: store (s, f_s) in
-//    the history): a launch copies up to 64 segments of like size into a
+//    the history): a launch copies up to 64 segments into a
 //    slot.
 // 3. Residual application on a skipped step (Section 3.1, block equation):
 //    the block stack's sum of predicted module outputs added to the
@@ -485,39 +485,57 @@ hipError_t launch_op(const void *const *src, int n, const double *w, int n_out,
 
 // ---- full-step push: segment gather into one slot --------------------------
 
-constexpr int kGatherMax = 64;
-constexpr uint32_t kGatherTile = 64;  // vectors per block, one per lane
+constexpr uint32_t kGatherTile = uint32_t(kGatherTileVecs);  // vectors per block, one per lane
 
 struct GatherArgs {
-  const void *src[kGatherMax];
-  uint64_t dst_vec[kGatherMax];  // vectors from the entry's base
-  uint64_t numel[kGatherMax];
+  const void *src[kGatherSegs];
+  uint64_t dst_vec[kGatherSegs];  // vectors from the entry's base
+  uint64_t numel[kGatherSegs];
+  GatherClass cls[kGatherClasses];
+  int32_t classes;
 };
 
-// Grid: x = tile of 64 vectors over a segment, y = segment.  Blocks past
-// their segment's end return at once, so no block searches for its segment;
-// the launches are planned with few of them (next_gather).  Bound by HBM, half reads and half
-// writes: one-wave blocks at full occupancy mix the two best (FLUX-1024 into
-// a contiguous slot: 487 us, 6.6 TB/s, against 514 with 256-lane blocks and
-// 500 or more with two or four vectors per lane at any limit on resident
-// blocks; into an interleaved lane 525 against 548).  Source reads and slot
-// writes are streaming (each byte is touched once per push), so both carry
-// the non-temporal hint.  Tiles are whole in the entry, not in the segment (a
-// segment's first one may begin with idle lanes): a tile that straddled
-// 128-byte lines would share them with its neighbours, which run on other
-// XCDs (6 fp32 segments of 41 MB that start anywhere in a line, into one of
-// six lanes: 82 us against 89 with tiles cut from the segment's start).  So
-// a tile lies in one chunk and its place is uniform.
-template <typename E>
+// Flat: x = tile of a segment, y = segment; blocks past their segment's end
+// return at once.  In classes a block finds its own by a scan of at most 16 and
+// its segment there by a division, both scalar (next_gather).  Bound by HBM, half
+// reads and half writes: one-wave blocks at full occupancy mix the two best
+// (FLUX-1024 into a contiguous slot: 485 us, 6.6 TB/s, against 514 with 256-lane
+// blocks and 500 or more with two or four vectors per lane at any limit on
+// resident blocks; into an interleaved lane 525 against 548).  Source reads and
+// slot writes are streaming (each byte is touched once per push), so both carry
+// the non-temporal hint.  For interleaved entries tiles are whole in the entry,
+// not in the segment (a segment's first one may begin with idle lanes), so a tile
+// lies in one chunk and its place is uniform, and one that straddled 128-byte
+// lines would share them with its neighbours, which run on other XCDs (6 fp32
+// segments of 41 MB that start anywhere in a line, into one of six lanes: 82 us
+// against 89 with tiles cut from the segment's start).  In contiguous slots whose
+// segments all start on 64 bytes they are cut from the segment's start, which
+// spares a load at the head of each block and lets the reads start on a line (DiT
+// steps of 10 to 30 us 1.5 to 2.3% faster, 36 fp32 tensors of 57 MB 639 us -> 622).
+template <typename E, bool kFlat, bool kWhole>  // kWhole: tiles whole in the entry
 __global__ __launch_bounds__(64) void gather_kernel(GatherArgs a, char *__restrict__ slot,
                                                     uint64_t super) {
   constexpr int kVec = 16 / int(sizeof(E));
-  const int s = int(blockIdx.y);
+  uint32_t s = blockIdx.y, tile = blockIdx.x;
+  if constexpr (!kFlat) {
+    int32_t p = 0;
+    for (int32_t q = 1; q < a.classes; ++q)
+      if (blockIdx.x >= a.cls[q].block) p = q;
+    const GatherClass c = a.cls[p];
+    const uint32_t b = blockIdx.x - c.block;
+    s = __umulhi(b, c.inverse);  // b / tiles, or one less
+    tile = b - s * c.tiles;
+    if (tile >= c.tiles) {
+      ++s;
+      tile -= c.tiles;
+    }
+    s += uint32_t(c.seg);
+  }
   const uint64_t numel = a.numel[s];
   const uint32_t n_full = uint32_t(numel / kVec);
   const uint32_t rem = uint32_t(numel % kVec);
-  const uint32_t lead = uint32_t(a.dst_vec[s]) & (kGatherTile - 1);
-  const uint32_t first = blockIdx.x * kGatherTile;
+  const uint32_t lead = kWhole ? uint32_t(a.dst_vec[s]) & (kGatherTile - 1) : 0u;
+  const uint32_t first = tile * kGatherTile;
   const uint32_t lane = threadIdx.x;
   if (first > n_full + lead) return;
   u32x4 *dst = reinterpret_cast<u32x4 *>(slot) +
@@ -877,29 +895,35 @@ int launch_combine(int dtype, const void *const *src, int n, const double *w, in
 
 int launch_gather(int dtype, void *slot_base, GatherSeg *segs, int n_segs, int64_t super_vecs,
                   hipStream_t stream) {
-  static_assert(kGatherMax == kGatherSegs && int64_t(kGatherTile) == kGatherTileVecs,
-                "the tables and tiles that the launches are planned for");
   n_segs = order_segments(segs, n_segs);
   const int64_t vec = elems_per_vec(dtype);
   GatherArgs a;
-  for (int at = 0, used = 0; at < n_segs; at += used) {
-    uint32_t tiles = 0;
-    used = next_gather(segs + at, n_segs - at, vec, &tiles);
+  for (int at = 0; at < n_segs;) {
+    const GatherPlan plan = next_gather(segs + at, n_segs - at, vec, super_vecs);
     memset(&a, 0, sizeof a);
-    for (int j = 0; j < used; ++j) {
+    for (int j = 0; j < plan.segs; ++j) {
       const GatherSeg &g = segs[at + j];
       a.src[j] = g.src;
       a.dst_vec[j] = uint64_t(g.dst_offset / vec);
       a.numel[j] = uint64_t(g.numel);
     }
+    memcpy(a.cls, plan.cls, sizeof(GatherClass) * size_t(plan.classes));
+    a.classes = plan.classes;
+    at += plan.segs;
     char *slot = static_cast<char *>(slot_base);
-    const dim3 grid{tiles, static_cast<uint32_t>(used), 1u};
-    const uint64_t sv = uint64_t(super_vecs);
-    if (elem_bytes(dtype) == 2)
-      hipLaunchKernelGGL(gather_kernel<uint16_t>, grid, dim3(kGatherTile), 0, stream, a, slot, sv);
-    else
-      hipLaunchKernelGGL(gather_kernel<float>, grid, dim3(kGatherTile), 0, stream, a, slot, sv);
-    hipError_t e = hipGetLastError();
+    const dim3 grid = plan.flat ? dim3(plan.widest, uint32_t(plan.segs)) : dim3(plan.blocks);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(kGatherTile), 0, stream, a, slot,
+                         uint64_t(super_vecs));
+      return hipGetLastError();
+    };
+    auto typed = [&](auto elem) {
+      using E = decltype(elem);
+      if (plan.whole)
+        return launch(plan.flat ? gather_kernel<E, true, true> : gather_kernel<E, false, true>);
+      return launch(plan.flat ? gather_kernel<E, true, false> : gather_kernel<E, false, false>);
+    };
+    const hipError_t e = elem_bytes(dtype) == 2 ? typed(uint16_t()) : typed(float());
     if (e != hipSuccess) return fail(CHEB_E_HIP, "push launch failed: %s", hipGetErrorString(e));
   }
   return ok();

@@ -8,7 +8,8 @@
 // budget set by stub_gather_batches_ok() says how many succeed before one
 // fails, so a push that fails part-way through them can be tested on the CPU.
 // The budget starts at 0 (every copy fails).  Each launch must take 1 to 64
-// segments, cover them with its tiles and leave few of those without work.
+// segments, cover them with its classes' tiles, leave few of those without work
+// and give the kernel's division the right segment.
 #include <atomic>
 
 #include "internal.h"
@@ -29,28 +30,54 @@ int launch_combine(int, const void *const *, int, const double *, int, void *con
   return fail(CHEB_E_HIP, "host-only build: no device launch");
 }
 
-int launch_gather(int dtype, void *, GatherSeg *segs, int n_segs, int64_t, hipStream_t) {
+int launch_gather(int dtype, void *, GatherSeg *segs, int n_segs, int64_t super_vecs,
+                  hipStream_t) {
   const int vec = elems_per_vec(dtype);
   n_segs = order_segments(segs, n_segs);
-  for (int at = 0, used = 0, launch = 0; at < n_segs; at += used, ++launch) {
-    uint32_t tiles = 0;
-    used = next_gather(segs + at, n_segs - at, vec, &tiles);
-    int64_t idle = 0;
-    for (int j = at; j < at + used; ++j) {
-      const int64_t first = segs[j].dst_offset / vec % kGatherTileVecs;
-      const int64_t end = first + (segs[j].numel + vec - 1) / vec;
-      const int64_t left = int64_t(tiles) - (end + kGatherTileVecs - 1) / kGatherTileVecs;
-      if (segs[j].numel <= 0 || left < 0)
-        return fail(CHEB_E_INVAL, "copy launch %d does not cover segment %d", launch, j);
-      idle += left;
+  for (int at = 0, launch = 0; at < n_segs; ++launch) {
+    const GatherPlan p = next_gather(segs + at, n_segs - at, vec, super_vecs);
+    if (p.segs < 1 || p.segs > kGatherSegs || p.classes < 1 || p.classes > kGatherClasses)
+      return fail(CHEB_E_INVAL, "copy launch %d of %d segments", launch, p.segs);
+    uint32_t block = 0;
+    int64_t flat_idle = 0;
+    for (int c = 0; c < p.classes; ++c) {
+      const GatherClass &k = p.cls[c];
+      const int end = c + 1 < p.classes ? p.cls[c + 1].seg : p.segs;
+      int64_t idle = 0;
+      if (k.block != block || (c == 0 && k.seg != 0) || end <= k.seg || k.tiles < 1)
+        return fail(CHEB_E_INVAL, "copy launch %d: class %d does not follow", launch, c);
+      for (int j = k.seg; j < end; ++j) {
+        const GatherSeg &g = segs[at + j];
+        const int64_t tail =
+            gather_lead(g.dst_offset / vec, p.whole) + (g.numel + vec - 1) / vec;
+        if (!p.whole && (super_vecs != kChunkVecs || g.dst_offset / vec % 4 != 0))
+          return fail(CHEB_E_INVAL, "copy launch %d: a tile across chunks or sectors", launch);
+        const int64_t left = int64_t(k.tiles) - (tail + kGatherTileVecs - 1) / kGatherTileVecs;
+        if (g.numel <= 0 || left < 0)
+          return fail(CHEB_E_INVAL, "copy launch %d does not cover segment %d", launch, j);
+        idle += left;
+        flat_idle += left + int64_t(p.widest) - k.tiles;
+        if (p.widest < k.tiles) return fail(CHEB_E_INVAL, "copy launch %d: too narrow", launch);
+        // The kernel's division, for the segment's first and last tile.
+        for (uint32_t b : {uint32_t(j - k.seg) * k.tiles, uint32_t(j - k.seg + 1) * k.tiles - 1}) {
+          uint32_t q = uint32_t((uint64_t(b) * k.inverse) >> 32);
+          if (b - q * k.tiles >= k.tiles) ++q;
+          if (q != uint32_t(j - k.seg) || b - q * k.tiles >= k.tiles)
+            return fail(CHEB_E_INVAL, "copy launch %d: block %u in segment %u", launch, b, q);
+        }
+      }
+      block += uint32_t(end - k.seg) * k.tiles;
+      if (idle > 24576 && idle * 8 > int64_t(end - k.seg) * k.tiles + 8 * 64)
+        return fail(CHEB_E_INVAL, "copy launch %d: %lld idle tiles", launch, (long long)idle);
     }
-    if (used < 1 || used > kGatherSegs || idle > 16384)
-      return fail(CHEB_E_INVAL, "copy launch %d of %d segments, %lld idle tiles", launch, used,
-                  (long long)idle);
+    if (p.flat ? flat_idle > 10240 && p.classes > 1 : flat_idle <= 10240)
+      return fail(CHEB_E_INVAL, "copy launch %d: %lld idle tiles", launch, (long long)flat_idle);
+    if (block != p.blocks) return fail(CHEB_E_INVAL, "copy launch %d: %u blocks", launch, block);
     if (g_gather_batches_ok.fetch_sub(1) <= 0) {
       g_gather_batches_ok.store(0);
       return fail(CHEB_E_HIP, "host-only build: copy launch %d refused", launch);
     }
+    at += p.segs;
   }
   return ok();
 }

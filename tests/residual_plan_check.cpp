@@ -4,7 +4,8 @@
 // say.  Random segment maps (gaps, overlaps, up to 8 intervals in one launch
 // and more in launches of their own, more segments over one element than a
 // table holds) in both layouts, with, without and in place of a residual,
-// against the plain sum over the segments.
+// against the plain sum over the segments.  Pushes of random layouts, from like
+// sizes to all different ones, go through the stub's check of their launches.
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -118,10 +119,31 @@ static void one(int seed) {
   free(arena);
 }
 
+// The arena is never dereferenced.
+static void pushes(int seed) {
+  g_seed = seed;
+  std::mt19937_64 rng(uint64_t(seed) + 1000);
+  const int layout = seed % 2 ? CHEB_LAYOUT_INTERLEAVED : CHEB_LAYOUT_SLOTS;
+  const int dtype = int(rng() % 3), segs = 1 + int(rng() % 200), kinds = 1 + int(rng() % 40);
+  std::vector<int64_t> size(kinds), numel(segs);
+  for (int64_t &n : size) n = int64_t(rng() >> (38 + rng() % 26));  // to 2^26
+  for (int64_t &n : numel) n = size[rng() % size.size()];
+  size_t bytes = 0;
+  if (cheb_cache_arena_bytes_ex(2, dtype, numel.data(), segs, layout, &bytes) != CHEB_OK) return;
+  void *arena = reinterpret_cast<void *>(uintptr_t(1) << 44);
+  cheb_cache *c = nullptr;
+  if (bytes == 0) return;
+  CHECK(cheb_cache_create_ex(&c, 2, dtype, numel.data(), segs, layout, arena, bytes) == CHEB_OK);
+  std::vector<const void *> src(segs, arena);
+  CHECK(cheb_cache_push(c, 1.0, src.data(), nullptr) == CHEB_OK);
+  CHECK(cheb_cache_destroy(c) == CHEB_OK);
+}
+
 int main() {
   stub_residual_on_host(1);
   stub_gather_batches_ok(1 << 30);
   for (int seed = 0; seed < 300; ++seed) one(seed);
+  for (int seed = 0; seed < 3000; ++seed) pushes(seed);
   // Image and text tokens: two intervals, one launch.
   const int64_t numel[] = {64, 16, 80}, off[] = {16, 0, 0};
   alignas(16) static float buf[160], x[80];

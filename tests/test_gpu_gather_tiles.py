@@ -1,5 +1,5 @@
 """The push's 64-vector tiles: segments around a tile's end, ragged and empty
-ones, very unlike sizes (several launches, largest first), equal ones that
+ones, very unlike sizes (in classes of like size, largest first), equal ones that
 start anywhere in a tile, and more segments than one launch takes, read back
 bit for bit with zeroed padding."""
 import pytest
@@ -17,6 +17,7 @@ SIZES = {
     "unlike": [5, 16385 * 512, 3, 16385 * 512 + 9, 700, 16000 * 512, 8],
     "alike_shifted": [528] * 70,               # tiles per segment vary with its place
     "many": [(j * 37) % 2000 for j in range(150)],
+    "all_unlike": [int(500 * 1.25 ** j) for j in range(35)],   # more sizes than classes
 }
 
 
