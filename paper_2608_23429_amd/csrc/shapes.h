@@ -151,7 +151,7 @@ struct ResShape {
 //  - contiguous ones beyond: up to 6 segments, and to 9 for up to 4 entries, 2
 //    waves, as 5 divided among 4 leave three idle for half of the time (5 entries
 //    of 5 segments, cu 43: 58.8, 69.5 with 4, 58.0 lanes); one entry of up to 31
-//    single runs (24 segments, cu 54: 61.6 against 64.0 in pairs); the others 4
+//    single runs to cu 64 (24 segments, cu 54: 61.6 against 64.0 in pairs); the others 4
 //    waves in pairs, few blocks (9072 tiles of 57 segments, 3 entries: 251 with
 //    2, 262 with 4 of single runs; 15 segments, 2 entries: 84 with 4, 99 with 2;
 //    FLUX-1024's reduction, one entry of 57 segments: 270 with 3, 283 with one
@@ -171,8 +171,8 @@ inline ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, bool
   if (upto(16) && few) {
     if (ncover == 2 || upto(4)) return {1, 0};
     if (!contiguous) return {ns >= 5 && !upto(6) ? 4 : 1, 0};
-    if (upto(12) || ns == 3 || ns == 4) return {1, 0};
-    return ns <= 2 ? ResShape{1, 0, 2} : ResShape{1, 0, 1, 16};
+    if (upto(12) || ns == 1 || ns == 3 || ns == 4) return {1, 0};
+    return ns == 2 ? ResShape{1, 0, 2} : ResShape{1, 0, 1, 16};
   }
   if (contiguous) {
     if (few) {
@@ -187,10 +187,10 @@ inline ResShape residual_shape(int ns, int vec, int ncover, uint32_t tiles, bool
     if (upto(16)) return ncover >= 7 && ncover <= 12 && ns >= 3 ? ResShape{1, 0, 1, 16}
                                                                 : ResShape{1, 0, 2};
     if (upto(24)) return {1, 0, 2};
-    if (ns == 1 && ncover <= 9) return {upto(32) ? 1 : 2, 0};
+    if (ns == 1 && ncover <= 9 && upto(64)) return {upto(32) ? 1 : 2, 0};
     if (upto(32)) return {1, 0, 2, 16};
     if (ns == 1 && ncover < 24) return {2, 0, 2};
-    if (ns == 1) return ncover < 32 ? ResShape{4, 8} : ResShape{4, 3, 2};
+    if (ns == 1) return ncover < 32 && upto(64) ? ResShape{4, 8} : ResShape{4, 3, 2};
     if (ncover <= 6 || (ncover <= 9 && ns <= 4)) return {2, 8};
     if (ncover <= 9) return {4, ns <= 6 || upto(64) ? 3 : 2, 2};
     if (ns >= 5) return {4, 2, 2};
